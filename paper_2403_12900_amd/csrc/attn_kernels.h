@@ -34,7 +34,8 @@ struct AttnArgs {
   void* act;              // output, K-block-major over H * hd
   float* part;            // [flat split][H][hd + 4]: m, l, -, -, o[hd]
   int32_t* cnt;           // [rows][Hkv] arrived splits; zero between launches
-  int n_rows, H, Hkv, G, mb, bpw, Rp;
+  int n_rows, H, Hkv, G, mb, bpw;
+  ActRec rec;             // layout of act
   float qscale;           // log2(e) / sqrt(hd)
   RowSlotPos rows;
   int split_start[kRows + 1];  // first flat split index of each row; [n_rows] = total
@@ -299,7 +300,7 @@ __device__ __forceinline__ void attn_decode_unit(const AttnArgs& a, int f, int k
 #pragma unroll
     for (int k = 0; k < EPW; ++k) {
       const int n0 = hq * HD + 16 * (wave * EPW + k) + 4 * g;
-      store_act4<AP>(act, a.Rp, b, n0, R[k][0] * inv, R[k][1] * inv, R[k][2] * inv, R[k][3] * inv);
+      store_act4<AP>(act, a.rec, b, n0, R[k][0] * inv, R[k][1] * inv, R[k][2] * inv, R[k][3] * inv);
     }
     return;
   }
@@ -376,7 +377,8 @@ __device__ __forceinline__ void merge_splits(const AttnArgs& a, int b, int kvh, 
       }
       M = Mn;
     }
-    act_store<AP>(act, a.Rp, b, hq * HD + dd, Ov / L);
+    const float out = Ov / L;
+    act_store<AP, 1>(act, a.rec, b, hq * HD + dd, &out);
   }
 }
 

@@ -86,13 +86,32 @@ struct F32 {
 };
 
 // Activation buffers (the MFMA B operand of the next projection) are
-// K-block-major: K-block kb of part q (hi, then mid / lo) of row b is a 64-byte run at
-// element offset ((kb * parts + q) * Rp + b) * kblk, Rp = padded rows.  The
-// 16 rows of one part of one K-block are therefore 1 KiB of consecutive
-// bytes, which is exactly what one 16-byte-per-lane load of a wave reads.
+// K-block-major: the 16 rows of one part (hi, then mid / lo) of K-block kb and
+// 16-row tile t are 1 KiB of consecutive bytes, 64 pieces of 16 bytes, at
+// ((kb * parts + q) * Rp + 16 t) * 64 bytes.  Within it piece (row r, K-group
+// g) sits at r * rs + g * gs:
+//   * fragment order (rs = 1, gs = 16): the piece of MFMA lane r + 16 g is
+//     piece r + 16 g, so a wave load (or a direct load into LDS) of the tile
+//     reads consecutive bytes in lane order, 8 cache lines;
+//   * row order (rs = 4, gs = 1): a row's 64 bytes are consecutive, so a batch
+//     of a few rows touches only its own bytes (a row in fragment order lies
+//     in four cache lines).
+// Decode passes of one 16-row tile use row order, everything else fragment
+// order (act_rec).  Measured on MI355X: prefill projections 7-13% faster in
+// fragment order (their activation fragments arrive in lane order, one cache
+// line per 8 lanes), 64-row decode projections 8-11%; at 1-8 rows row order
+// keeps a batch's lines to its own rows.
+struct ActRec {
+  int Rp;      // padded rows
+  int rs, gs;  // 16-byte pieces between rows of a tile, between K-groups
+};
+constexpr __host__ __device__ __forceinline__ ActRec act_rec(int Rp) {
+  return Rp <= 16 ? ActRec{Rp, 4, 1} : ActRec{Rp, 1, 16};
+}
 template <class P>
-__device__ __forceinline__ size_t act_offset(int Rp, int b, int k, int part) {
-  return (static_cast<size_t>(k / P::kblk * P::parts + part) * Rp + b) * P::kblk + k % P::kblk;
+__device__ __forceinline__ size_t act_offset(const ActRec& r, int b, int k, int part) {
+  return (static_cast<size_t>(k / P::kblk * P::parts + part) * r.Rp + (b & ~15)) * P::kblk +
+         ((b & 15) * r.rs + k % P::kblk / P::per16 * r.gs) * P::per16 + k % P::per16;
 }
 
 // A K tile of the KV cache (16 positions x head_dim) is stored in MFMA
@@ -122,17 +141,28 @@ __device__ __forceinline__ int vtile_offset(int t, int dd) {
   }
 }
 
-// Stores activation value v of row b, feature k as its P::parts parts: each
-// part is the storage rounding of what the earlier parts leave (exact fp32
-// differences).
-template <class P>
-__device__ __forceinline__ void act_store(typename P::elem* act, int Rp, int b, int k, float v) {
-  float r = v;
+// Stores N consecutive activation values of row b from feature k0 (a multiple
+// of N; N divides the elements of a 16-byte piece) as their P::parts parts:
+// each part is the storage rounding of what the earlier parts leave (exact
+// fp32 differences).  One store of N elements per part.
+template <class P, int N>
+__device__ __forceinline__ void act_store(typename P::elem* act, const ActRec& rec, int b, int k0, const float* v) {
+  typename P::elem* dst = act + act_offset<P>(rec, b, k0, 0);
+  float r[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) r[i] = v[i];
 #pragma unroll
   for (int q = 0; q < P::parts; ++q) {
-    const typename P::elem e = P::from_f32(r);
-    act[act_offset<P>(Rp, b, k, q)] = e;
-    r -= P::to_f32(e);
+    struct alignas(N * sizeof(typename P::elem)) {
+      typename P::elem e[N];
+    } out;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      out.e[i] = P::from_f32(r[i]);
+      r[i] -= P::to_f32(out.e[i]);
+    }
+    __builtin_memcpy(__builtin_assume_aligned(dst + static_cast<size_t>(q) * rec.Rp * P::kblk, sizeof(out)), &out,
+                     sizeof(out));
   }
 }
 

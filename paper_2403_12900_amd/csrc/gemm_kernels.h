@@ -183,6 +183,7 @@ __device__ __forceinline__ void stream_gemm_tiles(const uint4* __restrict__ W, c
   // c % 8; for three parts, columns 8-15 of fragment 1 (part 3: the next
   // K-block's part 0, or past the last K-block's record, inside the buffer)
   // are zeroed after the load.
+  constexpr ActRec xr = act_rec(16 * JT);
   const int xpart = Rp * 4;                  // uint4 per (K-block, part)
   const int xstep = PK ? 2 * xpart : xpart;  // uint4 between a lane's fragments
   int xoff[JT];
@@ -190,10 +191,10 @@ __device__ __forceinline__ void stream_gemm_tiles(const uint4* __restrict__ W, c
   for (int j = 0; j < JT; ++j) {
     if constexpr (PK) {
       const int c = lane & 15, r = c & 7;
-      xoff[j] = (c >> 3) * xpart + (r < n_rows ? r : 0) * 4 + (lane >> 4);
+      xoff[j] = (c >> 3) * xpart + (r < n_rows ? r : 0) * xr.rs + (lane >> 4) * xr.gs;
     } else {
       const int b = 16 * j + (lane & 15);
-      xoff[j] = (b < n_rows ? b : 0) * 4 + (lane >> 4);
+      xoff[j] = (b < n_rows ? 64 * j + (lane & 15) * xr.rs : 0) + (lane >> 4) * xr.gs;
     }
   }
   const bool zero_hi = PK && PARTS == 3 && (lane & 15) >= 8;  // packed (lo | 0): columns 8-15 are zero
@@ -440,12 +441,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_stream_gemm_qkv(const uint4* __r
 
 // Stores four consecutive features n0..n0+3 of row b into an activation buffer.
 template <class P>
-__device__ __forceinline__ void store_act4(typename P::elem* act, int Rp, int b, int n0, float v0, float v1, float v2,
-                                           float v3) {
-  act_store<P>(act, Rp, b, n0, v0);
-  act_store<P>(act, Rp, b, n0 + 1, v1);
-  act_store<P>(act, Rp, b, n0 + 2, v2);
-  act_store<P>(act, Rp, b, n0 + 3, v3);
+__device__ __forceinline__ void store_act4(typename P::elem* act, const ActRec& rec, int b, int n0, float v0, float v1,
+                                           float v2, float v3) {
+  const float v[4] = {v0, v1, v2, v3};
+  act_store<P, 4>(act, rec, b, n0, v);
 }
 
 // QKV projection -> RMSNorm scale -> RoPE on q and k -> q to the attention
@@ -542,7 +541,8 @@ struct EpiQKV {
 template <class P>
 struct EpiResid {
   static constexpr bool kNorm = false;
-  int n_rows, d, Rp;
+  int n_rows, d;
+  ActRec rec;                   // layout of act
   float* x;                     // residual [rows][d]
   typename P::elem* act;        // next activation (K-block-major)
 
@@ -578,7 +578,7 @@ struct EpiResid {
       xv.z += acc[j][2];
       xv.w += acc[j][3];
       *xp = xv;
-      store_act4<P>(act, Rp, b, n0, xv.x, xv.y, xv.z, xv.w);
+      store_act4<P>(act, rec, b, n0, xv.x, xv.y, xv.z, xv.w);
     }
   }
 };
@@ -588,7 +588,8 @@ struct EpiResid {
 template <class P>
 struct EpiSwiGLU {
   static constexpr bool kNorm = true;
-  int n_rows, dnorm, Rp;
+  int n_rows, dnorm;
+  ActRec rec;                   // layout of act
   float eps;
   typename P::elem* act;        // h, K-block-major over d_ff
 
@@ -609,8 +610,8 @@ struct EpiSwiGLU {
       const float g0 = acc[j][0] * s, g1 = acc[j][1] * s, u0 = acc[j][2] * s, u1 = acc[j][3] * s;
       const float h0 = g0 / (1.f + __expf(-g0)) * u0;
       const float h1 = g1 / (1.f + __expf(-g1)) * u1;
-      act_store<P>(act, Rp, b, j0, h0);
-      act_store<P>(act, Rp, b, j0 + 1, h1);
+      const float h[2] = {h0, h1};
+      act_store<P, 2>(act, rec, b, j0, h);
     }
   }
 };

@@ -32,7 +32,7 @@ struct PrefillTile {
 template <class P>
 __global__ __launch_bounds__(64) void k_embed_rows(const typename P::elem* __restrict__ emb,
                                                    const PrefillRow* __restrict__ rows, float* x,
-                                                   typename P::elem* act, int d, int V, int Rp) {
+                                                   typename P::elem* act, int d, int V, ActRec rec) {
   const int b = blockIdx.y;
   const int n0 = 4 * (blockIdx.x * 64 + threadIdx.x);
   if (n0 >= d) return;
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(64) void k_embed_rows(const typename P::elem* __res
   const typename P::elem* e = emb + static_cast<size_t>(t) * d + n0;
   const float v0 = P::to_f32(e[0]), v1 = P::to_f32(e[1]), v2 = P::to_f32(e[2]), v3 = P::to_f32(e[3]);
   *reinterpret_cast<float4*>(x + static_cast<size_t>(b) * d + n0) = make_float4(v0, v1, v2, v3);
-  store_act4<P>(act, Rp, b, n0, v0, v1, v2, v3);
+  store_act4<P>(act, rec, b, n0, v0, v1, v2, v3);
 }
 
 // RMSNorm scale of each row (unit gains): rs[b] = 1 / sqrt(mean(x_b^2) + eps).
@@ -121,8 +121,7 @@ __device__ __forceinline__ void lds_stage_barrier() {
 // owning a WN x WM block of 16 x 16 MFMA tiles.  Per K-block the work-group's
 // operands -- TN weight fragments and TM x parts activation fragments, 1 KiB
 // each -- go from global memory straight into LDS (global_load_lds, no
-// register staging) in MFMA lane order: weight fragments are stored that way,
-// and for activation fragments lane r + 16 g fetches row r's K-group g.  Three
+// register staging) in MFMA lane order, the order both are stored in.  Three
 // LDS stages (three separate arrays, so the compiler tracks each stage's
 // loads on its own) keep two K-blocks in flight; each K-block costs one
 // barrier: wait for its own loads, barrier (which also frees the stage read
@@ -175,7 +174,6 @@ __global__ __launch_bounds__(NW * 64) void k_tile_gemm(const uint4* __restrict__
   }
   const int wn = wave % TS::GN, wm = wave / TS::GN;
   const size_t xpart = static_cast<size_t>(Rp) * 4;  // uint4 per (K-block, part)
-  const int xlane = (lane & 15) * 4 + (lane >> 4);   // uint4 of an activation fragment MFMA lane `lane` needs
 
   auto issue = [&](int kb, uint4(*dst)[64]) {
 #pragma unroll
@@ -188,7 +186,7 @@ __global__ __launch_bounds__(NW * 64) void k_tile_gemm(const uint4* __restrict__
       } else {
         const int a = f - TN, q = a / TM, tt = a % TM;
         const int r0 = min(m0 + 16 * tt, Rp - 16);
-        src = X + (static_cast<size_t>(kb) * LP + q) * xpart + static_cast<size_t>(r0) * 4 + xlane;
+        src = X + (static_cast<size_t>(kb) * LP + q) * xpart + static_cast<size_t>(r0) * 4 + lane;
       }
       __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)&dst[f][0], 16, 0, 0);
     }
@@ -318,7 +316,8 @@ struct EpiQKVRows {
 // O and down projections: residual add, new residual as the next activation.
 template <class P>
 struct EpiResidRows {
-  int M, d, Rp;
+  int M, d;
+  ActRec rec;
   float* x;
   typename P::elem* act;
 
@@ -333,14 +332,15 @@ struct EpiResidRows {
     xv.z += acc[2];
     xv.w += acc[3];
     *xp = xv;
-    store_act4<P>(act, Rp, b, n0, xv.x, xv.y, xv.z, xv.w);
+    store_act4<P>(act, rec, b, n0, xv.x, xv.y, xv.z, xv.w);
   }
 };
 
 // Gate/up (interleaved rows): RMSNorm scale, h = SiLU(gate) * up.
 template <class P>
 struct EpiSwiGLURows {
-  int M, Rp;
+  int M;
+  ActRec rec;
   const float* rs;
   typename P::elem* act;
 
@@ -350,8 +350,8 @@ struct EpiSwiGLURows {
     const int j0 = 8 * nt + 2 * (lane >> 4);
     const float s = rs[b];
     const float g0 = acc[0] * s, g1 = acc[1] * s, u0 = acc[2] * s, u1 = acc[3] * s;
-    act_store<P>(act, Rp, b, j0, g0 / (1.f + __expf(-g0)) * u0);
-    act_store<P>(act, Rp, b, j0 + 1, g1 / (1.f + __expf(-g1)) * u1);
+    const float h[2] = {g0 / (1.f + __expf(-g0)) * u0, g1 / (1.f + __expf(-g1)) * u1};
+    act_store<P, 2>(act, rec, b, j0, h);
   }
 };
 
@@ -370,7 +370,7 @@ template <class P, class AP, int HD>
 __global__ __launch_bounds__(256) void k_attn_prefill(const float* __restrict__ q, const void* kcv, const void* vcv,
                                                       const int32_t* __restrict__ bt,
                                                       const PrefillTile* __restrict__ tiles, void* actv, int H,
-                                                      int Hkv, int mb, int Rp, float qscale) {
+                                                      int Hkv, int mb, ActRec rec, float qscale) {
   using E = typename P::elem;
   using Blk = KVBlock<P, HD>;
   constexpr bool kBf16 = sizeof(E) == 2;
@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256) void k_attn_prefill(const float* __restrict__ 
   typename AP::elem* act = static_cast<typename AP::elem*>(actv);
 #pragma unroll
   for (int e = 0; e < NE; ++e)
-    store_act4<AP>(act, Rp, tile.row0 + r0 + c, hq * HD + 16 * e + 4 * g, O[e][0] * inv, O[e][1] * inv,
+    store_act4<AP>(act, rec, tile.row0 + r0 + c, hq * HD + 16 * e + 4 * g, O[e][0] * inv, O[e][1] * inv,
                    O[e][2] * inv, O[e][3] * inv);
 }
 
@@ -527,7 +527,8 @@ __global__ __launch_bounds__(256) void k_attn_prefill(const float* __restrict__ 
 struct GatherArgs {
   const float* x;
   void* act;
-  int d, Rp, n;
+  int d, n;
+  ActRec rec;
   int src[kRows];
 };
 template <class P>
@@ -536,7 +537,7 @@ __global__ __launch_bounds__(64) void k_gather_rows(GatherArgs a) {
   const int n0 = 4 * (blockIdx.x * 64 + threadIdx.x);
   if (n0 >= a.d || k >= a.n) return;
   const float4 v = *reinterpret_cast<const float4*>(a.x + static_cast<size_t>(a.src[k]) * a.d + n0);
-  store_act4<P>(static_cast<typename P::elem*>(a.act), a.Rp, k, n0, v.x, v.y, v.z, v.w);
+  store_act4<P>(static_cast<typename P::elem*>(a.act), a.rec, k, n0, v.x, v.y, v.z, v.w);
 }
 
 }  // namespace sprk

@@ -436,7 +436,7 @@ spr_status launch_attention(spr_model* m, const AttnArgs& a) {
 
 // Attention arguments of one layer over rs (kv splits of bpw blocks per wave).
 template <class P, class KP>
-AttnArgs attention_args(spr_model* m, int l, const RowSet& rs, const RowSlotPos& sp, int Rp, int bpw, void* act,
+AttnArgs attention_args(spr_model* m, int l, const RowSet& rs, const RowSlotPos& sp, const ActRec& rec, int bpw, void* act,
                         const DecodeScratch& sc) {
   const spr::Dims& d = m->d;
   Ptrs p{m->ws, &m->lay};
@@ -454,7 +454,7 @@ AttnArgs attention_args(spr_model* m, int l, const RowSet& rs, const RowSlotPos&
   a.G = d.G;
   a.mb = d.mb;
   a.bpw = bpw;
-  a.Rp = Rp;
+  a.rec = rec;
   a.qscale = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(d.hd)));
   a.rows = sp;
   a.split_start[0] = 0;
@@ -482,7 +482,7 @@ spr_status forward(spr_model* m, const RowSet& rs, const int32_t* tok_in, int32_
   Ptrs p{m->ws, &m->lay};
   const int n = rs.n;
   const int JT = n <= 16 ? 1 : n <= 32 ? 2 : n <= 64 ? 4 : 8;
-  const int Rp = 16 * JT;
+  const ActRec rec = act_rec(16 * JT);
   using E = typename P::elem;
   RowSlotPos sp;
   std::memcpy(sp.slot, rs.slot, sizeof(sp.slot));
@@ -498,7 +498,7 @@ spr_status forward(spr_model* m, const RowSet& rs, const int32_t* tok_in, int32_
     ea.n_rows = n;
     ea.d = d.d;
     ea.V = d.V;
-    ea.Rp = Rp;
+    ea.rec = rec;
     std::memcpy(ea.slot, rs.slot, sizeof(ea.slot));
     std::memcpy(ea.tok, rs.tok, sizeof(ea.tok));
     k_embed<QKVIn<P>><<<dim3(ceil_div(d.d / 4, 64), n), 64, 0, m->st>>>(ea);
@@ -556,23 +556,23 @@ spr_status forward(spr_model* m, const RowSet& rs, const int32_t* tok_in, int32_
       if ((st = launch_gemm<QKVIn<P>>(m, d.nt_qkv, p.wqkv(l), p.act(0), d.kb_d, JT, e, room)) != SPR_OK) return st;
     }
     {
-      const AttnArgs a = attention_args<P, KP>(m, l, rs, sp, Rp, bpw, p.act(1), sc);
+      const AttnArgs a = attention_args<P, KP>(m, l, rs, sp, rec, bpw, p.act(1), sc);
       st = d.hd == 128 ? launch_attention<P, KP, 128>(m, a) : launch_attention<P, KP, 64>(m, a);
       if (st != SPR_OK) return st;
     }
     {
-      EpiResid<P> e{n, d.d, Rp, p.x(), reinterpret_cast<E*>(p.act(0))};
+      EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       if ((st = launch_gemm<P>(m, d.nt_o, p.wo(l), p.act(1), d.kb_o, JT, e, room)) != SPR_OK) return st;
     }
     {
-      EpiSwiGLU<P> e{n, d.d, Rp, d.eps, reinterpret_cast<E*>(p.act(1))};
+      EpiSwiGLU<P> e{n, d.d, rec, d.eps, reinterpret_cast<E*>(p.act(1))};
       if ((st = launch_gemm<P>(m, d.nt_13, p.w13(l), p.act(0), d.kb_d, JT, e, room)) != SPR_OK) return st;
     }
     if (l + 1 < d.L) {  // the new residual is the next layer's QKV input
-      EpiResid<QKVIn<P>> e{n, d.d, Rp, p.x(), reinterpret_cast<E*>(p.act(0))};
+      EpiResid<QKVIn<P>> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       if ((st = launch_gemm<P>(m, d.nt_2, p.w2(l), p.act(1), d.kb_f, JT, e, room)) != SPR_OK) return st;
     } else {            // ... or the LM head's
-      EpiResid<P> e{n, d.d, Rp, p.x(), reinterpret_cast<E*>(p.act(0))};
+      EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       if ((st = launch_gemm<P>(m, d.nt_2, p.w2(l), p.act(1), d.kb_f, JT, e, room)) != SPR_OK) return st;
     }
   }
@@ -610,19 +610,19 @@ spr_status launch_projection(spr_model* m, int projection, int layer, int n) {
   Ptrs p{m->ws, &m->lay};
   const SplitRoom room = split_room(workspace_scratch(m));
   const int JT = n <= 16 ? 1 : n <= 32 ? 2 : n <= 64 ? 4 : 8;
-  const int Rp = 16 * JT;
+  const ActRec rec = act_rec(16 * JT);
   using E = typename P::elem;
   switch (projection) {
     case 1: {
-      EpiResid<P> e{n, d.d, Rp, p.x(), reinterpret_cast<E*>(p.act(0))};
+      EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       return launch_gemm<P>(m, d.nt_o, p.wo(layer), p.act(1), d.kb_o, JT, e, room);
     }
     case 2: {
-      EpiSwiGLU<P> e{n, d.d, Rp, d.eps, reinterpret_cast<E*>(p.act(1))};
+      EpiSwiGLU<P> e{n, d.d, rec, d.eps, reinterpret_cast<E*>(p.act(1))};
       return launch_gemm<P>(m, d.nt_13, p.w13(layer), p.act(0), d.kb_d, JT, e, room);
     }
     case 3: {  // as in every layer but the last
-      EpiResid<QKVIn<P>> e{n, d.d, Rp, p.x(), reinterpret_cast<E*>(p.act(0))};
+      EpiResid<QKVIn<P>> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       return launch_gemm<P>(m, d.nt_2, p.w2(layer), p.act(1), d.kb_f, JT, e, room);
     }
     default: {
@@ -649,12 +649,12 @@ struct PrefillChunk {
 };
 
 template <class P, class KP, int HD>
-void launch_attn_prefill(spr_model* m, int layer, const PrefillChunk& ch, int Rp) {
+void launch_attn_prefill(spr_model* m, int layer, const PrefillChunk& ch, const ActRec& rec) {
   const spr::Dims& d = m->d;
   Ptrs p{m->ws, &m->lay};
   const float qscale = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(d.hd)));
   k_attn_prefill<KP, P, HD><<<dim3(ch.n_tiles, d.H), 256, 0, m->st>>>(p.q(), p.kc(layer), p.vc(layer), p.bt(),
-                                                                       p.ptile(), p.act(1), d.H, d.Hkv, d.mb, Rp,
+                                                                       p.ptile(), p.act(1), d.H, d.Hkv, d.mb, rec,
                                                                        qscale);
 }
 
@@ -698,9 +698,10 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   using E = typename P::elem;
   const int C = ch.C;
   const int Rp = 128 * ceil_div(C, 128);
+  const ActRec rec = act_rec(Rp);
   const dim3 grid_d(ceil_div(d.d / 4, 64), C);
   k_embed_rows<QKVIn<P>><<<grid_d, 64, 0, m->st>>>(reinterpret_cast<const E*>(p.emb()), p.prow(), p.x(),
-                                                   reinterpret_cast<E*>(p.act(0)), d.d, d.V, Rp);
+                                                   reinterpret_cast<E*>(p.act(0)), d.d, d.V, rec);
   SPR_LAUNCHED(m, "k_embed_rows");
   for (int l = 0; l < d.L; ++l) {
     k_row_rscale<<<ceil_div(C, 4), 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
@@ -732,21 +733,21 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
       }
     }
     if (d.hd == 128) {
-      launch_attn_prefill<P, KP, 128>(m, l, ch, Rp);
+      launch_attn_prefill<P, KP, 128>(m, l, ch, rec);
     } else {
-      launch_attn_prefill<P, KP, 64>(m, l, ch, Rp);
+      launch_attn_prefill<P, KP, 64>(m, l, ch, rec);
     }
     {
-      EpiResidRows<P> e{C, d.d, Rp, p.x(), reinterpret_cast<E*>(p.act(0))};
+      EpiResidRows<P> e{C, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       launch_tile_gemm<P>(m->st, p.wo(l), p.act(1), d.nt_o, d.kb_o, Rp, e);
     }
     k_row_rscale<<<ceil_div(C, 4), 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
     {
-      EpiSwiGLURows<P> e{C, Rp, p.rs(), reinterpret_cast<E*>(p.act(1))};
+      EpiSwiGLURows<P> e{C, rec, p.rs(), reinterpret_cast<E*>(p.act(1))};
       launch_tile_gemm<P>(m->st, p.w13(l), p.act(0), d.nt_13, d.kb_d, Rp, e);
     }
     {  // the new residual is the next layer's QKV input (the prompt's last rows reach the LM head from x)
-      EpiResidRows<QKVIn<P>> e{C, d.d, Rp, p.x(), reinterpret_cast<E*>(p.act(0))};
+      EpiResidRows<QKVIn<P>> e{C, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       launch_tile_gemm<P>(m->st, p.w2(l), p.act(1), d.nt_2, d.kb_f, Rp, e);
     }
     SPR_LAUNCHED(m, "prefill layer");
@@ -759,7 +760,7 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
     g.x = p.x();
     g.act = p.act(1);
     g.d = d.d;
-    g.Rp = 16 * JT;
+    g.rec = act_rec(16 * JT);
     g.n = n;
     for (int k = 0; k < n; ++k) g.src[k] = ch.emit_row[k];
     k_gather_rows<P><<<dim3(ceil_div(d.d / 4, 64), n), 64, 0, m->st>>>(g);
