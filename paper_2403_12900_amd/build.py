@@ -1,8 +1,10 @@
 """Builds the HIP decode library (libsprout.so, gfx950) and the host-only
 bookkeeping test library (libsprout_host.so) in the package directory."""
+import concurrent.futures
 import os
 import subprocess
 import sys
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
@@ -11,7 +13,7 @@ HOST_LIB = os.path.join(PKG, "libsprout_host.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 HIP_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # Packed fp32 instructions stay off: ordinary float code only.
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # MFMA accumulators in VGPRs: epilogues and the softmax rescale operate on
@@ -30,11 +32,19 @@ def _run(cmd, verbose):
     subprocess.run(cmd, check=True)
 
 
+# Translation units of libsprout.so, the slowest to compile first; compiled in parallel.
+SOURCES = ["panel_qkv.hip", "panel_resid.hip", "panel_mlp.hip", "sprout.hip", "host_state.cpp"]
+
+
 def build(verbose: bool = True) -> None:
-    srcs = [os.path.join(CSRC, "sprout.hip"), os.path.join(CSRC, "host_state.cpp")]
-    tmp = LIB + ".tmp"
-    _run([HIPCC, *HIP_FLAGS, *srcs, "-o", tmp], verbose)
-    os.replace(tmp, LIB)
+    with tempfile.TemporaryDirectory() as d:
+        objs = [os.path.join(d, s + ".o") for s in SOURCES]
+        with concurrent.futures.ThreadPoolExecutor(len(SOURCES)) as ex:
+            list(ex.map(lambda so: _run([HIPCC, *HIP_FLAGS, "-c", os.path.join(CSRC, so[0]), "-o", so[1]], verbose),
+                        zip(SOURCES, objs)))
+        tmp = LIB + ".tmp"
+        _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp], verbose)
+        os.replace(tmp, LIB)
     tmp = HOST_LIB + ".tmp"
     _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
           os.path.join(CSRC, "host_state.cpp"), os.path.join(CSRC, "host_test_api.cpp"), "-o", tmp], verbose)

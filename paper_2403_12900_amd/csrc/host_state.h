@@ -36,20 +36,17 @@ struct Dims {
   float rope_base, eps;
 };
 
-// Split-K shapes of the decode projections past 8 rows (16-row tiles per
-// group, K slices): O and down, gate/up, QKV.
-struct SplitShape {
-  int rt, s;
-};
-constexpr SplitShape kSplitO{2, 4}, kSplitGU{4, 2}, kSplitQKV{4, 4};
+// Bounds on what one split-K launch uses (projections of 9 rows and more):
+// partial sums in bytes, by whether the pass has at most 64 rows (every decode
+// pass) or up to 128, and arrival counters.  The launch rule keeps to them, so
+// that the same pass takes the same split in every scratch it may run in.
+constexpr size_t kSplitPartBytes = size_t{16} << 20, kSplitPartBytesWide = size_t{28} << 20;
+int split_counters(const Dims& d);
 
-// Bounds on what the split-K launches of any decode pass of the model use:
-// partial-sum floats and arrival counters.
-struct SplitNeed {
-  size_t part_floats;
-  int counters;
-};
-SplitNeed split_need(const Dims& d);
+// Whether spr_decode_step_static_scratch's fixed array holds the model's
+// widths: the limits of the entry point (d_model 32784, d_ff 30840, query, key
+// and value rows 30840).
+bool static_scratch_widths(const Dims& d);
 
 struct Layout {
   size_t wqkv, wo, w13, w2;        // per-layer strides of the tiled weights (bytes)

@@ -13,13 +13,15 @@
 //     k_stream_gemm<EpiResid>    x += h W2^T (and the next QKV input)
 //   k_stream_gemm<EpiLogits>     RMSNorm(x) Wlm^T, per-tile greedy candidates
 //   k_argmax_final               tok[slot] = lowest index of the row maximum
+// (past 8 rows the projections run as k_panel_gemm / k_panel_gemm_qkv).
 // A prefill chunk (up to 4096 prompt rows of one or more requests) runs the
 // same layer stack on tiled, compute-bound kernels:
 //   k_embed_rows; per layer k_row_rscale, k_tile_gemm<EpiQKVRows> (query
 //   tiles, then key and value tiles),
 //   k_attn_prefill (causal, 16 queries per MFMA), k_tile_gemm<EpiResidRows>,
 //   k_row_rscale, k_tile_gemm<EpiSwiGLURows>, k_tile_gemm<EpiResidRows>;
-//   then k_gather_rows of the rows that end a prompt, and the decode LM head.
+//   then k_gather_rows of the rows that end a prompt, and the decode LM head
+//   (bf16 chunks of at most 128 rows run a decode pass's projections instead).
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -32,6 +34,7 @@
 #include "attn_kernels.h"
 #include "gemm_kernels.h"
 #include "host_state.h"
+#include "panel_launch.h"
 #include "prefill_kernels.h"
 #include "step_kernels.h"
 #include "wgen_kernels.h"
@@ -47,7 +50,7 @@ static_assert(spr::kMaxRows == sprk::kRows, "decode pass size");
 // slices), arrival counters, LM-head greedy candidates.  Host code never passes the array's name to a kernel (on the
 // host it is only a stand-in symbol): it resolves the array's device address
 // once per device at init (static_scratch_address) and passes that.
-constexpr size_t kStaticPartBytes = size_t{16} << 20;
+constexpr size_t kStaticPartBytes = spr::kSplitPartBytes;
 constexpr size_t kStaticCntBytes = size_t{64} << 10;
 constexpr size_t kStaticAmaxBytes = (size_t{8} << 20) - kStaticCntBytes;
 constexpr size_t kStaticScratchBytes = kStaticPartBytes + kStaticCntBytes + kStaticAmaxBytes;  // 24 MiB
@@ -215,16 +218,8 @@ DecodeScratch workspace_scratch(const spr_model* m) {
   return DecodeScratch{p.part(), p.cnt(), p.amax(), spr::kMaxSplits, m->lay.part_floats, m->lay.n_cnt};
 }
 
-// Room for split-K partials and arrival counters (see SplitK): the regions of
-// the attention split partials and counters, which hold what any pass's
-// split-K launches need (spr::split_need) and which every launch that uses
-// them leaves zero.
-struct SplitRoom {
-  float* part = nullptr;  // null: no split-K
-  int32_t* cnt = nullptr;
-  size_t part_floats = 0;
-  int n_cnt = 0;
-};
+// Rows up to which a decode pass takes the register-streaming kernel.
+constexpr int kStreamRows = 8;
 
 SplitRoom split_room(const DecodeScratch& sc) { return SplitRoom{sc.part, sc.cnt, sc.part_floats, sc.n_cnt}; }
 
@@ -254,11 +249,6 @@ spr_status init_weights(spr_model* m) {
   return SPR_OK;
 }
 
-// Activation format of the QKV projection's input: all 24 bits of the fp32
-// residual for bf16 models (three parts), the plain format otherwise.
-template <class P>
-using QKVIn = std::conditional_t<std::is_same_v<P, BF16>, BF16x3, P>;
-
 // Rows of one forward pass.
 struct RowSet {
   int n = 0;
@@ -269,159 +259,42 @@ struct RowSet {
   int hist_idx[kRows];  // token-history index of the row's token, -1 = none
 };
 
-// Whether an epilogue is a residual update (O and down).
-template <class E>
-struct IsResid : std::false_type {};
-template <class F>
-struct IsResid<EpiResid<F>> : std::true_type {};
-
-// Split-K pays (see SplitK) once a work-group's activation range holds at
-// least this many K-block parts per 16-row tile (at two parts, 384 KiB of
-// activations per work-group at 16 rows): measured on the 7B projections at
-// 12-32 rows, it is then 1-7 us faster per launch; below (O and gate/up at
-// 9-16 rows) the slices' publication costs more than it saves.
-constexpr int kSplitMinParts = 384;
-
-// Split-K launch (see SplitK) of S slices per group of RT tiles, WAVES waves
-// per work-group; false (nothing launched) when the tiles do not divide into
-// groups or the room is too small.
-template <class P, int JT, int WAVES, int RT, int S, int U, class Epi>
-bool launch_split(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, const Epi& epi,
-                  const SplitRoom& room) {
-  const int groups = NT / RT;
-  if (room.part == nullptr || NT % RT != 0 || groups > room.n_cnt ||
-      static_cast<size_t>(groups) * S * SplitKPairs<JT, RT, Epi::kNorm>::value * 128 > room.part_floats)
-    return false;
-  k_stream_gemm_split<P, JT, WAVES, Epi, RT, U, S><<<groups * S, WAVES * 64, 0, st>>>(
-      w, x, KB, 16 * JT, epi.n_rows, epi, SplitK{room.part, room.cnt});
-  return true;
-}
-
-// Launch shape of a projection, from sweeps over the 7B projection shapes on
-// MI355X at 1..32 rows:
-//   * at 9..32 rows, where a work-group's activation range holds at least
-//     kSplitMinParts K-block parts per tile: split-K across work-groups (for
-//     the 7B shapes down at 9..32 rows, O and gate/up at 17..32); never the
-//     LM head;
-//   * wide projections (>= 1024 16-row tiles: gate/up, LM head) at up to 32
-//     rows: one-wave work-groups, each streaming two whole tiles over the
-//     full K -- long contiguous streams and no cross-wave reduction;
-//   * projections of 512..1023 tiles at 17..64 rows: four waves split K for
-//     two tiles, so each activation fragment feeds two weight fragments;
+// Projection of a pass over epi.n_rows rows (activation record of row_tiles
+// row tiles): up to kStreamRows rows on the register-streaming kernel, more on
+// the panel kernel.  A matrix of kPanelMatrix K-block tiles (576 MB) or more,
+// whose tiles split evenly over the CUs whatever the group size, takes the
+// panel kernel at any row count (70B gate/up, 3 rows: 135 us against 143; the
+// 7B shape's matrices are 0 to 2 us faster streamed).  Streaming shapes, from
+// sweeps over the 7B projections on MI355X at 1 to 8 rows:
+//   * wide projections (>= 1024 16-row tiles: gate/up, LM head): one-wave
+//     work-groups, each streaming two whole tiles over the full K -- long
+//     contiguous streams and no cross-wave reduction;
 //   * everything else: four waves split K for one tile.
-// PK: packed rows (at most 8 rows, two activation parts per fragment).
-template <class P, int JT, bool PK, class Epi>
-void launch_gemm_shape(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, const Epi& epi,
-                       const SplitRoom& room) {
-  const int Rp = 16 * JT, n = epi.n_rows;
-  constexpr int XF = StreamFrags<P, PK>::value;  // activation fragments per K-block and tile
-  if constexpr (!PK && JT <= 2) {
-    // Past 8 rows, with enough activation bytes per work-group: split-K.
-    // Shapes from sweeps of the 7B projections at 12-32 rows.
-    if (KB * JT * P::parts >= kSplitMinParts) {
-      if constexpr (IsResid<Epi>::value) {
-        // O and down: two tiles per group, four slices of two waves.
-        if (launch_split<P, JT, 2, spr::kSplitO.rt, spr::kSplitO.s, 4>(st, NT, w, x, KB, epi, room)) return;
-      } else if constexpr (std::is_same_v<Epi, EpiSwiGLU<P>>) {
-        // gate/up: four tiles per group, two one-wave slices.
-        if (launch_split<P, JT, 1, spr::kSplitGU.rt, spr::kSplitGU.s, 4>(st, NT, w, x, KB, epi, room)) return;
-      }
-    }
-  }
-  if constexpr (JT <= 2) {
-    if (NT >= 1024 && NT % 2 == 0) {
-      constexpr int U = XF == 3 ? (JT == 1 ? 4 : 2) : (JT == 1 ? 8 : 4);
-      k_stream_gemm<P, JT, 1, Epi, 2, U, true, PK><<<NT / 2, 64, 0, st>>>(w, x, KB, Rp, n, epi);
-      return;
-    }
-  }
-  if constexpr (JT >= 2 && JT <= 4) {
-    if (NT >= 512 && NT % 2 == 0) {
-      k_stream_gemm<P, JT, 4, Epi, 2, StreamDepth<2 * JT * P::parts>::value, true><<<NT / 2, 256, 0, st>>>(
-          w, x, KB, Rp, n, epi);
-      return;
-    }
-  }
-  k_stream_gemm<P, JT, 4, Epi, 1, StreamDepth<JT * XF>::value, true, PK><<<NT, 256, 0, st>>>(w, x, KB, Rp, n, epi);
-}
-
-// QKV of bf16 models (three-part input, see k_stream_gemm_qkv): four waves
-// splitting K of one tile per work-group with packed rows (at most 8); at
-// 9..32 rows split-K across work-groups; without room for its partials, two
-// tiles per work-group (measured on the 7B shape at 16 rows: 1.2% less
-// decode-step time than one).
-template <int JT, bool PK, class Epi>
-void launch_qkv_shape(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, const Epi& epi,
-                      const SplitRoom& room) {
-  const int Rp = 16 * JT, n = epi.n_rows;
-  const int q_tiles = epi.H * epi.hd / 16;
-  if constexpr (!PK && JT <= 2) {
-    // Past 8 rows: split-K, four tiles per group, four slices of two waves
-    // (9-16 rows) or one (17-32 rows); from sweeps of the 7B QKV projection.
-    constexpr int RT = spr::kSplitQKV.rt, S = spr::kSplitQKV.s, WV = JT == 1 ? 2 : 1;
-    const int groups = NT / RT;
-    if (KB * JT * 3 >= kSplitMinParts && room.part != nullptr && NT % RT == 0 && q_tiles % RT == 0 &&
-        groups <= room.n_cnt &&
-        static_cast<size_t>(groups) * S * SplitKPairs<JT, RT, true>::value * 128 <= room.part_floats) {
-      k_stream_gemm_qkv<JT, WV, Epi, RT, 4, 4, false, S>
-          <<<groups * S, WV * 64, 0, st>>>(w, x, KB, Rp, n, epi, q_tiles, SplitK{room.part, room.cnt});
-      return;
-    }
-  }
-  if constexpr (!PK && JT <= 4) {
-    if (NT % 2 == 0 && q_tiles % 2 == 0) {
-      k_stream_gemm_qkv<JT, 4, Epi, 2, StreamDepth<2 * JT * 2>::value, StreamDepth<2 * JT * 3>::value, false>
-          <<<NT / 2, 256, 0, st>>>(w, x, KB, Rp, n, epi, q_tiles);
-      return;
-    }
-  }
-  if constexpr (JT == 8) {  // (more rows than a decode pass holds) every tile takes all three parts
-    k_stream_gemm<BF16x3, JT, 4, Epi, 1, StreamDepth<JT * 3>::value, true><<<NT, 256, 0, st>>>(w, x, KB, Rp, n, epi);
-  } else {
-    constexpr int X2 = StreamFrags<BF16, PK>::value, X3 = StreamFrags<BF16x3, PK>::value;
-    k_stream_gemm_qkv<JT, 4, Epi, 1, StreamDepth<JT * X2>::value, StreamDepth<JT * X3>::value, PK>
-        <<<NT, 256, 0, st>>>(w, x, KB, Rp, n, epi, q_tiles);
-  }
-}
-
+// bf16 activations are packed (two parts per fragment, at most 8 rows).
+constexpr int64_t kPanelMatrix = 576 << 10;
 template <class P, class Epi>
-spr_status launch_gemm(spr_model* m, int NT, const char* W, const char* X, int KB, int JT, const Epi& epi,
-                       const SplitRoom& room = {}) {
+spr_status launch_gemm(spr_model* m, int NT, const char* W, const char* X, int KB, const Epi& epi,
+                       const SplitRoom& room) {
   const uint4* w = reinterpret_cast<const uint4*>(W);
   const uint4* x = reinterpret_cast<const uint4*>(X);
-  if constexpr (P::parts == 3) {
-    switch (JT) {
-      case 1:
-        if (epi.n_rows <= 8) {
-          launch_qkv_shape<1, true>(m->st, NT, w, x, KB, epi, room);
-        } else {
-          launch_qkv_shape<1, false>(m->st, NT, w, x, KB, epi, room);
-        }
-        break;
-      case 2: launch_qkv_shape<2, false>(m->st, NT, w, x, KB, epi, room); break;
-      case 4: launch_qkv_shape<4, false>(m->st, NT, w, x, KB, epi, room); break;
-      case 8: launch_qkv_shape<8, false>(m->st, NT, w, x, KB, epi, room); break;
-      default:
-        return fail(SPR_ERR_INVALID_ARG, "internal: unsupported row-tile count");
-    }
-    SPR_LAUNCHED(m, "k_stream_gemm_qkv");
+  const hipStream_t st = m->st;
+  const int n = epi.n_rows;
+  if (n > kStreamRows || (P::parts >= 2 && int64_t{NT} * KB >= kPanelMatrix)) {
+    launch_panel_gemm<P, Epi>(st, NT, w, x, KB, epi, room);
+    SPR_LAUNCHED(m, "k_panel_gemm");
     return SPR_OK;
   }
-  switch (JT) {
-    case 1:
-      if constexpr (P::parts >= 2) {
-        if (epi.n_rows <= 8) {
-          launch_gemm_shape<P, 1, true>(m->st, NT, w, x, KB, epi, room);
-          break;
-        }
-      }
-      launch_gemm_shape<P, 1, false>(m->st, NT, w, x, KB, epi, room);
-      break;
-    case 2: launch_gemm_shape<P, 2, false>(m->st, NT, w, x, KB, epi, room); break;
-    case 4: launch_gemm_shape<P, 4, false>(m->st, NT, w, x, KB, epi, room); break;
-    case 8: launch_gemm_shape<P, 8, false>(m->st, NT, w, x, KB, epi, room); break;
-    default:
-      return fail(SPR_ERR_INVALID_ARG, "internal: unsupported row-tile count");
+  constexpr int Rp = 16;
+  constexpr bool PK = P::parts >= 2;
+  constexpr int XF = StreamFrags<P, PK>::value;  // activation fragments per K-block
+  if constexpr (P::parts == 3) {                 // QKV: query tiles take two of the three parts
+    constexpr int X2 = StreamFrags<BF16, PK>::value;
+    k_stream_gemm_qkv<1, 4, Epi, 1, StreamDepth<X2>::value, StreamDepth<XF>::value, PK>
+        <<<NT, 256, 0, st>>>(w, x, KB, Rp, n, epi, epi.H * epi.hd / 16);
+  } else if (NT >= 1024 && NT % 2 == 0) {
+    k_stream_gemm<P, 1, 1, Epi, 2, 8, true, PK><<<NT / 2, 64, 0, st>>>(w, x, KB, Rp, n, epi);
+  } else {
+    k_stream_gemm<P, 1, 4, Epi, 1, StreamDepth<XF>::value, true, PK><<<NT, 256, 0, st>>>(w, x, KB, Rp, n, epi);
   }
   SPR_LAUNCHED(m, "k_stream_gemm");
   return SPR_OK;
@@ -472,6 +345,54 @@ int attn_blocks_per_cu(const spr::Dims& d) {
   return o;
 }
 
+// QKV projection of layer l over n rows (a decode pass, or a prefill chunk of
+// as many rows).
+template <class P, class KP>
+spr_status qkv_projection(spr_model* m, int l, int n, const RowSlotPos& rows, const SplitRoom& room) {
+  const spr::Dims& d = m->d;
+  Ptrs p{m->ws, &m->lay};
+  EpiQKV<P, KP> e{};
+  e.n_rows = n;
+  e.H = d.H;
+  e.Hkv = d.Hkv;
+  e.hd = d.hd;
+  e.mb = d.mb;
+  e.dnorm = d.d;
+  e.eps = d.eps;
+  e.q = p.q();
+  e.kc = reinterpret_cast<typename KP::elem*>(p.kc(l));
+  e.vc = reinterpret_cast<typename KP::elem*>(p.vc(l));
+  e.bt = p.bt();
+  e.rope = p.rope();
+  e.rows = rows;
+  return launch_gemm<QKVIn<P>>(m, d.nt_qkv, p.wqkv(l), p.act(0), d.kb_d, e, room);
+}
+
+// O, gate/up and down projections of layer l over n rows, from the attention
+// output to the next layer's QKV input (qkv_next) or the LM head's.
+template <class P>
+spr_status mlp_projections(spr_model* m, int l, int n, bool qkv_next, const SplitRoom& room) {
+  const spr::Dims& d = m->d;
+  Ptrs p{m->ws, &m->lay};
+  using E = typename P::elem;
+  const ActRec rec = act_rec(16 * row_tiles(n));
+  spr_status st;
+  {
+    EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
+    if ((st = launch_gemm<P>(m, d.nt_o, p.wo(l), p.act(1), d.kb_o, e, room)) != SPR_OK) return st;
+  }
+  {
+    EpiSwiGLU<P> e{n, d.d, rec, d.eps, reinterpret_cast<E*>(p.act(1))};
+    if ((st = launch_gemm<P>(m, d.nt_13, p.w13(l), p.act(0), d.kb_d, e, room)) != SPR_OK) return st;
+  }
+  if (qkv_next) {
+    EpiResid<QKVIn<P>> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
+    return launch_gemm<P>(m, d.nt_2, p.w2(l), p.act(1), d.kb_f, e, room);
+  }
+  EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
+  return launch_gemm<P>(m, d.nt_2, p.w2(l), p.act(1), d.kb_f, e, room);
+}
+
 // One forward pass over rs (rows: slot, position, emitted logits row).
 // tok_in != null: the inputs are tok_in[slot]; otherwise rs.tok.  Emitting
 // rows write their greedy token to tok_out[slot].
@@ -481,8 +402,7 @@ spr_status forward(spr_model* m, const RowSet& rs, const int32_t* tok_in, int32_
   const spr::Dims& d = m->d;
   Ptrs p{m->ws, &m->lay};
   const int n = rs.n;
-  const int JT = n <= 16 ? 1 : n <= 32 ? 2 : n <= 64 ? 4 : 8;
-  const ActRec rec = act_rec(16 * JT);
+  const ActRec rec = act_rec(16 * row_tiles(n));
   using E = typename P::elem;
   RowSlotPos sp;
   std::memcpy(sp.slot, rs.slot, sizeof(sp.slot));
@@ -538,43 +458,11 @@ spr_status forward(spr_model* m, const RowSet& rs, const int32_t* tok_in, int32_
   const SplitRoom room = split_room(sc);
   spr_status st;
   for (int l = 0; l < d.L; ++l) {
-    {
-      EpiQKV<P, KP> e{};
-      e.n_rows = n;
-      e.H = d.H;
-      e.Hkv = d.Hkv;
-      e.hd = d.hd;
-      e.mb = d.mb;
-      e.dnorm = d.d;
-      e.eps = d.eps;
-      e.q = p.q();
-      e.kc = reinterpret_cast<typename KP::elem*>(p.kc(l));
-      e.vc = reinterpret_cast<typename KP::elem*>(p.vc(l));
-      e.bt = p.bt();
-      e.rope = p.rope();
-      e.rows = sp;
-      if ((st = launch_gemm<QKVIn<P>>(m, d.nt_qkv, p.wqkv(l), p.act(0), d.kb_d, JT, e, room)) != SPR_OK) return st;
-    }
-    {
-      const AttnArgs a = attention_args<P, KP>(m, l, rs, sp, rec, bpw, p.act(1), sc);
-      st = d.hd == 128 ? launch_attention<P, KP, 128>(m, a) : launch_attention<P, KP, 64>(m, a);
-      if (st != SPR_OK) return st;
-    }
-    {
-      EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      if ((st = launch_gemm<P>(m, d.nt_o, p.wo(l), p.act(1), d.kb_o, JT, e, room)) != SPR_OK) return st;
-    }
-    {
-      EpiSwiGLU<P> e{n, d.d, rec, d.eps, reinterpret_cast<E*>(p.act(1))};
-      if ((st = launch_gemm<P>(m, d.nt_13, p.w13(l), p.act(0), d.kb_d, JT, e, room)) != SPR_OK) return st;
-    }
-    if (l + 1 < d.L) {  // the new residual is the next layer's QKV input
-      EpiResid<QKVIn<P>> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      if ((st = launch_gemm<P>(m, d.nt_2, p.w2(l), p.act(1), d.kb_f, JT, e, room)) != SPR_OK) return st;
-    } else {            // ... or the LM head's
-      EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      if ((st = launch_gemm<P>(m, d.nt_2, p.w2(l), p.act(1), d.kb_f, JT, e, room)) != SPR_OK) return st;
-    }
+    if ((st = qkv_projection<P, KP>(m, l, n, sp, room)) != SPR_OK) return st;
+    const AttnArgs a = attention_args<P, KP>(m, l, rs, sp, rec, bpw, p.act(1), sc);
+    st = d.hd == 128 ? launch_attention<P, KP, 128>(m, a) : launch_attention<P, KP, 64>(m, a);
+    if (st != SPR_OK) return st;
+    if ((st = mlp_projections<P>(m, l, n, l + 1 < d.L, room)) != SPR_OK) return st;
   }
   {
     EpiLogits<P> e{};
@@ -585,7 +473,7 @@ spr_status forward(spr_model* m, const RowSet& rs, const int32_t* tok_in, int32_
     e.logits = logits;
     e.part = sc.amax;
     std::memcpy(e.out_row, rs.out_row, sizeof(e.out_row));
-    if ((st = launch_gemm<P>(m, d.nt_lm, p.wlm(), p.act(0), d.kb_d, JT, e)) != SPR_OK) return st;
+    if ((st = launch_gemm<P>(m, d.nt_lm, p.wlm(), p.act(0), d.kb_d, e, room)) != SPR_OK) return st;
   }
   {
     ArgmaxArgs a{};
@@ -609,21 +497,20 @@ spr_status launch_projection(spr_model* m, int projection, int layer, int n) {
   const spr::Dims& d = m->d;
   Ptrs p{m->ws, &m->lay};
   const SplitRoom room = split_room(workspace_scratch(m));
-  const int JT = n <= 16 ? 1 : n <= 32 ? 2 : n <= 64 ? 4 : 8;
-  const ActRec rec = act_rec(16 * JT);
+  const ActRec rec = act_rec(16 * row_tiles(n));
   using E = typename P::elem;
   switch (projection) {
     case 1: {
       EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      return launch_gemm<P>(m, d.nt_o, p.wo(layer), p.act(1), d.kb_o, JT, e, room);
+      return launch_gemm<P>(m, d.nt_o, p.wo(layer), p.act(1), d.kb_o, e, room);
     }
     case 2: {
       EpiSwiGLU<P> e{n, d.d, rec, d.eps, reinterpret_cast<E*>(p.act(1))};
-      return launch_gemm<P>(m, d.nt_13, p.w13(layer), p.act(0), d.kb_d, JT, e, room);
+      return launch_gemm<P>(m, d.nt_13, p.w13(layer), p.act(0), d.kb_d, e, room);
     }
     case 3: {  // as in every layer but the last
       EpiResid<QKVIn<P>> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      return launch_gemm<P>(m, d.nt_2, p.w2(layer), p.act(1), d.kb_f, JT, e, room);
+      return launch_gemm<P>(m, d.nt_2, p.w2(layer), p.act(1), d.kb_f, e, room);
     }
     default: {
       EpiLogits<P> e{};
@@ -634,7 +521,7 @@ spr_status launch_projection(spr_model* m, int projection, int layer, int n) {
       e.logits = nullptr;
       e.part = p.amax();
       for (int r = 0; r < kRows; ++r) e.out_row[r] = -1;
-      return launch_gemm<P>(m, d.nt_lm, p.wlm(), p.act(0), d.kb_d, JT, e);
+      return launch_gemm<P>(m, d.nt_lm, p.wlm(), p.act(0), d.kb_d, e, room);
     }
   }
 }
@@ -646,6 +533,7 @@ spr_status launch_projection(spr_model* m, int projection, int layer, int n) {
 struct PrefillChunk {
   int C = 0, n_tiles = 0, n_emit = 0;
   int emit_row[kRows], emit_out[kRows], emit_slot[kRows], emit_hist[kRows];
+  RowSlotPos sp;  // the rows, when there are at most kRows
 };
 
 template <class P, class KP, int HD>
@@ -697,13 +585,31 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   Ptrs p{m->ws, &m->lay};
   using E = typename P::elem;
   const int C = ch.C;
-  const int Rp = 128 * ceil_div(C, 128);
+  // A bf16 chunk that a decode pass could hold runs its projections as a
+  // decode pass does: they are still bound by the weight stream (128 rows of
+  // the 7B shape, a layer's projections: 205 us against 345).
+  const bool small = P::parts >= 2 && C <= kRows;
+  const int Rp = small ? 16 * row_tiles(C) : 128 * ceil_div(C, 128);
   const ActRec rec = act_rec(Rp);
+  const SplitRoom room = split_room(workspace_scratch(m));
+  spr_status st;
   const dim3 grid_d(ceil_div(d.d / 4, 64), C);
   k_embed_rows<QKVIn<P>><<<grid_d, 64, 0, m->st>>>(reinterpret_cast<const E*>(p.emb()), p.prow(), p.x(),
                                                    reinterpret_cast<E*>(p.act(0)), d.d, d.V, rec);
   SPR_LAUNCHED(m, "k_embed_rows");
   for (int l = 0; l < d.L; ++l) {
+    if constexpr (P::parts >= 2) {
+      if (small) {
+        if ((st = qkv_projection<P, KP>(m, l, C, ch.sp, room)) != SPR_OK) return st;
+        if (d.hd == 128) {
+          launch_attn_prefill<P, KP, 128>(m, l, ch, rec);
+        } else {
+          launch_attn_prefill<P, KP, 64>(m, l, ch, rec);
+        }
+        if ((st = mlp_projections<P>(m, l, C, true, room)) != SPR_OK) return st;
+        continue;
+      }
+    }
     k_row_rscale<<<ceil_div(C, 4), 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
     {
       EpiQKVRows<P, KP> e{};
@@ -754,19 +660,17 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   }
   if (ch.n_emit == 0) return SPR_OK;
   const int n = ch.n_emit;
-  const int JT = n <= 16 ? 1 : n <= 32 ? 2 : n <= 64 ? 4 : 8;
   {
     GatherArgs g{};
     g.x = p.x();
     g.act = p.act(1);
     g.d = d.d;
-    g.rec = act_rec(16 * JT);
+    g.rec = act_rec(16 * row_tiles(n));
     g.n = n;
     for (int k = 0; k < n; ++k) g.src[k] = ch.emit_row[k];
     k_gather_rows<P><<<dim3(ceil_div(d.d / 4, 64), n), 64, 0, m->st>>>(g);
     SPR_LAUNCHED(m, "k_gather_rows");
   }
-  spr_status st;
   {
     EpiLogits<P> e{};
     e.n_rows = n;
@@ -776,7 +680,7 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
     e.logits = logits;
     e.part = p.amax();
     for (int k = 0; k < kRows; ++k) e.out_row[k] = k < n ? ch.emit_out[k] : -1;
-    if ((st = launch_gemm<P>(m, d.nt_lm, p.wlm(), p.act(1), d.kb_d, JT, e)) != SPR_OK) return st;
+    if ((st = launch_gemm<P>(m, d.nt_lm, p.wlm(), p.act(1), d.kb_d, e, room)) != SPR_OK) return st;
   }
   {
     ArgmaxArgs a{};
@@ -858,6 +762,12 @@ spr_status prefill_device(spr_model* m, int n, const int32_t* slots, const int32
     if (chunk_rows.empty()) return SPR_OK;
     ch.C = static_cast<int>(chunk_rows.size());
     ch.n_tiles = static_cast<int>(tiles.size());
+    if (ch.C <= kRows) {
+      for (int r = 0; r < kRows; ++r) {
+        ch.sp.slot[r] = r < ch.C ? chunk_rows[r].slot : 0;
+        ch.sp.pos[r] = r < ch.C ? chunk_rows[r].pos : 0;
+      }
+    }
     if (ch.n_tiles > spr::kPrefillTiles) return fail(SPR_ERR_INVALID_ARG, "internal: prefill tile table overflow");
     row_tabs.push_back(std::move(chunk_rows));
     tile_tabs.push_back(std::move(tiles));
@@ -1050,7 +960,7 @@ spr_status spr_init(const spr_config* cfg, uint64_t seed, void* dev_ws, size_t w
   hipError_t e = hipMemcpyAsync(p.rope(), rope.data(), rope.size() * sizeof(float), hipMemcpyHostToDevice, m->st);
   if (e == hipSuccess) e = hipMemsetAsync(p.bt(), 0, static_cast<size_t>(d.S) * d.mb * sizeof(int32_t), m->st);
   if (e == hipSuccess) e = hipMemsetAsync(p.act(0), 0, lay.act_bytes, m->st);
-  if (e == hipSuccess) e = hipMemsetAsync(p.cnt(), 0, static_cast<size_t>(spr::kMaxRows) * d.Hkv * sizeof(int32_t), m->st);
+  if (e == hipSuccess) e = hipMemsetAsync(p.cnt(), 0, static_cast<size_t>(lay.n_cnt) * sizeof(int32_t), m->st);
   if (e == hipSuccess) e = hipMemsetAsync(p.act(1), 0, lay.act_bytes, m->st);
   if (e == hipSuccess) e = hipMemsetAsync(p.x(), 0, static_cast<size_t>(spr::kPrefillRows) * d.d * sizeof(float), m->st);
   // The device error flag: mapped pinned host memory, written by kernels only
@@ -1139,11 +1049,9 @@ spr_status spr_decode_step_static_scratch(spr_model* m, int32_t n_active, const 
   const spr::Dims& d = m->d;
   const size_t per_split = static_cast<size_t>(d.H) * (d.hd + 4) * sizeof(float);
   const int max_splits = static_cast<int>(std::min<size_t>(spr::kMaxSplits, kStaticPartBytes / per_split));
-  const spr::SplitNeed sn = spr::split_need(d);
   if (static_cast<size_t>(spr::kMaxRows) * d.Hkv * sizeof(int32_t) > kStaticCntBytes ||
       static_cast<size_t>(d.nt_lm) * spr::kMaxRows * sizeof(float2) > kStaticAmaxBytes || max_splits < n_active ||
-      sn.part_floats * sizeof(float) > kStaticPartBytes ||
-      static_cast<size_t>(sn.counters) * sizeof(int32_t) > kStaticCntBytes)
+      !spr::static_scratch_widths(d) || spr::split_counters(d) * sizeof(int32_t) > kStaticCntBytes)
     return fail(SPR_ERR_INVALID_ARG, "decode_step_static_scratch: the model or batch exceeds the 24 MiB static "
                                      "scratch (at most 128 KV heads, vocab <= 130048, n_heads * (head_dim + 4) "
                                      "* 4 * n_active <= 16 MiB, d_ff <= 30840 and (n_heads + 2 * n_kv_heads) * "
@@ -1169,7 +1077,7 @@ spr_status spr_decode_step_static_scratch(spr_model* m, int32_t n_active, const 
   // Every call shares the array: the attention split counters and the
   // projections' split-K counters must start at zero (a fill kernel, which a
   // graph capture may record).
-  const int ncnt = std::max(n_active * d.Hkv, spr::split_need(d).counters);
+  const int ncnt = std::max(n_active * d.Hkv, spr::split_counters(d));
   k_zero_i32<<<ceil_div(ncnt, 256), 256, 0, m->st>>>(sc.cnt, ncnt);
   SPR_LAUNCHED(m, "k_zero_i32");
   if ((st = forward_any(m, rs, tok, tok, logits, nullptr, sc)) != SPR_OK) return st;

@@ -1,0 +1,38 @@
+"""Projections at the edges of their row ranges: the streaming kernel ends at 8 rows, and the panel kernel changes its
+row-tile count at 16, 32, 48, 64 and (prefill chunks) 96 and 128 rows.  The model's widths leave remainders everywhere:
+7 and 10 K-blocks (no multiple of a chunk's 2 or 4, and fewer than three chunks), 14, 25 and 21 weight tiles (no multiple
+of a work-group's), query tiles that end inside a work-group."""
+import numpy as np
+import pytest
+
+from oracle import llama_ref as R
+from paper_2403_12900_amd.configs import ModelConfig
+from tests._harness import DeviceRun, check_against_oracle, oracle_shape, say
+
+BF16_TOL, FP32_TOL = (5e-2, 1e-2), (1e-4, 1e-5)  # the gates of the parity tests
+
+
+def _model(bf16, kv_bf16=None):
+    return ModelConfig(n_layers=2, d_model=224, n_heads=5, n_kv_heads=5, head_dim=64, d_ff=200, vocab=333, bf16=bf16,
+                       kv_bf16=kv_bf16)
+
+
+# (requests, rows of the prefill, bf16 weights, bf16 KV cache)
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,rows,bf16,kv_bf16", [
+    (8, 8, True, True), (9, 9, True, True), (16, 33, True, False), (17, 65, True, True), (32, 96, True, True),
+    (33, 97, True, False), (48, 128, True, True), (49, 129, True, True), (64, 64, True, True), (9, 17, False, False),
+    (64, 70, False, False)])
+def test_rows_at_the_edges(n, rows, bf16, kv_bf16):
+    m = _model(bf16, kv_bf16)
+    say(f"rows at the edges: {n} requests, {rows} prompt rows, bf16={bf16} kv_bf16={kv_bf16}")
+    rng = np.random.default_rng(1000 * n + rows)
+    lens = [rows // n + (i < rows % n) for i in range(n)]
+    prompts = [rng.integers(0, m.vocab, size=s).astype(np.int32) for s in lens]
+    stops = [3] * n
+    run = DeviceRun(m, 91, prompts, stops)
+    st = check_against_oracle(run, R.Weights(oracle_shape(m), 91), prompts, stops, range(n),
+                              *(BF16_TOL if bf16 else FP32_TOL))
+    say(st)
+    assert st["rows"] == 3 * n
+    run.close()
