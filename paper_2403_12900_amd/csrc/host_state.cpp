@@ -116,7 +116,10 @@ Layout layout(const Dims& d) {
   l.off_q = take(static_cast<size_t>(kPrefillRows) * d.H * d.hd * sizeof(float));
   // Partials of decode attention's KV splits, or of the projections' split-K
   // slices (never both in one launch).
-  l.part_floats = std::max(static_cast<size_t>(kMaxSplits) * d.H * (d.hd + 4), kSplitPartBytesWide / sizeof(float));
+  // Prefill projections of full-size models split K too.
+  const bool large = d.dtype == SPR_BF16 && static_cast<int64_t>(d.nt_13) * d.kb_d * kFragBytes >= (int64_t{32} << 20);
+  l.part_floats = std::max(static_cast<size_t>(kMaxSplits) * d.H * (d.hd + 4),
+                           (large ? kPrefillPartBytes : kSplitPartBytesWide) / sizeof(float));
   l.off_part = take(l.part_floats * sizeof(float));
   // Arrival counters: decode attention's, one per (row, KV head), or the
   // split-K groups'; zero between launches.
@@ -131,9 +134,10 @@ Layout layout(const Dims& d) {
 }
 
 int split_counters(const Dims& d) {
-  // One per wave of a launch, each with one tile or more, in whole work-groups
-  // of at most eight waves.
-  return std::max({d.nt_qkv, d.nt_o, d.nt_13, d.nt_2, d.nt_lm}) + 8;
+  // Decode: one per wave of a launch, each with one tile or more, in whole
+  // work-groups of at most eight waves.  Prefill: four per output tile of a
+  // split launch, whose tiles are at most a few per CU.
+  return std::max({d.nt_qkv + 8, d.nt_o + 8, d.nt_13 + 8, d.nt_2 + 8, d.nt_lm + 8, 4096});
 }
 
 bool static_scratch_widths(const Dims& d) { return d.nt_2 <= 2049 && d.nt_13 <= 3855 && d.nt_qkv <= 1927; }

@@ -41,6 +41,8 @@ struct Dims {
 // pass) or up to 128, and arrival counters.  The launch rule keeps to them, so
 // that the same pass takes the same split in every scratch it may run in.
 constexpr size_t kSplitPartBytes = size_t{16} << 20, kSplitPartBytesWide = size_t{28} << 20;
+// Partial sums of a prefill chunk's split-K projections (full-size models).
+constexpr size_t kPrefillPartBytes = size_t{100} << 20;
 int split_counters(const Dims& d);
 
 // Whether spr_decode_step_static_scratch's fixed array holds the model's

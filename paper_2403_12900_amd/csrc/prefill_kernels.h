@@ -42,96 +42,103 @@ __global__ __launch_bounds__(64) void k_embed_rows(const typename P::elem* __res
   store_act4<P>(act, rec, b, n0, v0, v1, v2, v3);
 }
 
-// RMSNorm scale of each row (unit gains): rs[b] = 1 / sqrt(mean(x_b^2) + eps).
-// One wave per row.
-__global__ __launch_bounds__(256) void k_row_rscale(const float* __restrict__ x, float* rs, int M, int d, float eps) {
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (b >= M) return;
-  const float* xr = x + static_cast<size_t>(b) * d;
-  float s = 0.f;
-  for (int k = 4 * lane; k < d; k += 256) {
-    const float4 v = *reinterpret_cast<const float4*>(xr + k);
-    s = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, s))));
-  }
-  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-  if (lane == 0) rs[b] = rsqrtf(s / static_cast<float>(d) + eps);
+// Tiled projection: out[b][n] = sum_k W[n][k] x[b][k] for rows b < M, fused
+// with the op that follows (Epi).  An output tile is TN weight tiles (16
+// output features each) x TM row tiles (16 rows each); the four waves (2 x 2)
+// of a work-group each own a TN/2 x TM/2 block of 16 x 16 MFMA tiles.  Per
+// K-block the tile's operands -- TN weight fragments and TM x parts activation
+// fragments, 1 KiB each -- go from global memory straight into LDS
+// (global_load_lds, no register staging) in MFMA lane order, the order both
+// are stored in.  NST LDS stages keep NST - 1 K-blocks in flight; each K-block
+// costs one barrier: wait for its own loads, barrier (which also frees the
+// stage read one K-block earlier), issue the loads NST - 1 K-blocks ahead,
+// multiply.  Weight tiles past NT re-read tile NT - 1 and row tiles past Rp
+// re-read the last one; neither is stored.
+//
+// What bounds it (MI355X, 4096 rows of the 7B gate/up projection): its MFMAs
+// alone take about 770 us, its loads alone 560 (256 x 256) to 800 us (128 x
+// 128), and they overlap only across work-groups, since within one every wave
+// waits at the same barrier.  So a shape is chosen for two or more work-groups
+// per CU -- two stages of 256 features x 128 rows are 64 KiB of LDS (80 KiB
+// with three parts) -- instead of one larger work-group with deeper stages:
+// 4096 rows of O (7B) take 188 us (1460 TFLOP/s issued) against 262 us for one
+// eight-wave 256 x 256 work-group of three stages.
+//
+// K is split over gridDim.z slices (kSplit) where the tiles alone leave the
+// chip idle: each wave publishes its partial sums with agent-coherent stores
+// and counts itself in, and the last slice's wave to arrive adds the partials
+// in slice order -- bitwise reproducible -- and runs the epilogue (no work-
+// group waits on another).  Cutting all tiles' K-blocks into one equal range
+// per resident work-group instead, so that none idles, was 1.4 times slower:
+// the work-groups of an XCD then read different K-blocks and share nothing in
+// its L2.
+struct TileSplit {
+  float* part;    // [tile][slice][wave][tile fragment][2][64 lanes][2] floats
+  int32_t* cnt;   // [tile][wave] arrived slices; zero between launches
+};
+constexpr int kTileWaves = 4;
+template <int TN, int TM>
+constexpr size_t tile_slice_floats() {  // floats a wave publishes per slice
+  return static_cast<size_t>(TN / 2) * (TM / 2) * 256;
 }
 
-// Tiled projection: out[b][n] = sum_k W[n][k] x[b][k] for rows b < M, fused
-// with the op that follows (Epi).  A work-group computes TN weight tiles (16
-// output features each) x TM row tiles (16 rows each) with NW waves, each
-// owning a WN x WM block of 16 x 16 MFMA tiles.  Per K-block the work-group's
-// operands -- TN weight fragments and TM x parts activation fragments, 1 KiB
-// each -- go from global memory straight into LDS (global_load_lds, no
-// register staging) in MFMA lane order, the order both are stored in.  Three
-// LDS stages (three separate arrays, so the compiler tracks each stage's
-// loads on its own) keep two K-blocks in flight; each K-block costs one
-// barrier: wait for its own loads, barrier (which also frees the stage read
-// one K-block earlier), issue the loads two K-blocks ahead, multiply.  Weight
-// tiles past NT re-read tile NT - 1 and row tiles past Rp re-read the last
-// one; neither is stored.
-// The operands a K-block moves from L2 into LDS, TN + parts x TM fragments,
-// bound these kernels before MFMA does: the largest shape (256 features x 256
-// rows, eight waves) moves half the bytes per product of 128 x 128.
-template <int TN, int TM, int NW>
-struct TileShape {
-  static constexpr int GN = NW == 8 ? 2 : TN == 4 && TM == 8 ? 1 : 2;  // waves along features
-  static constexpr int GM = NW / GN;                                  // waves along rows
-  static constexpr int WN = TN / GN, WM = TM / GM;
-  static_assert(GN * GM == NW && WN * GN == TN && WM * GM == TM, "tile shape");
-};
-
 // LP: parts per K-block of the activation record (the first P::parts are used).
-template <class P, int TN, int TM, class Epi, int NW = 4, int LP = P::parts>
-__global__ __launch_bounds__(NW * 64) void k_tile_gemm(const uint4* __restrict__ W, const uint4* __restrict__ X,
-                                                       int NT, int KB, int Rp, Epi epi) {
-  constexpr int PARTS = P::parts;
+// Grid: (weight tiles / TN, row tiles / TM, K slices).
+template <class P, int TN, int TM, int NST, bool kSplit, class Epi, int LP = P::parts>
+__global__ __launch_bounds__(256, 2) void k_tile_gemm(const uint4* W, const uint4* X, int NT, int KB, int Rp,
+                                                      TileSplit ts, Epi epi) {
+  constexpr int PARTS = P::parts, NW = kTileWaves;
   static_assert(LP >= PARTS, "the record holds the parts used");
   constexpr int NFRAG = TN + TM * PARTS;
-  static_assert(NFRAG % NW == 0, "fragments per stage must split over the waves");
-  constexpr int L = NFRAG / NW;  // loads per wave per stage
-  using TS = TileShape<TN, TM, NW>;
-  constexpr int WN = TS::WN, WM = TS::WM;
-  __shared__ uint4 st0[NFRAG][64];
-  __shared__ uint4 st1[NFRAG][64];
-  __shared__ uint4 st2[NFRAG][64];
+  constexpr int LW = TN / NW, L = (NFRAG + NW - 1) / NW;  // loads per wave per stage: weights, all
+  static_assert(TN % NW == 0, "weight fragments split over the waves");
+  constexpr int WN = TN / 2, WM = TM / 2;
+  __shared__ uint4 lds[NST * NFRAG * 64];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = wave % 2, wm = wave / 2;
   // Work-groups go to the eight XCDs in turn (linear id mod 8), and each XCD
   // has its own L2.  XCD x takes the contiguous range of tiles from x * total
   // / 8 in an order that runs over groups of four row tiles, the row tile
-  // fastest: the 32 work-groups an XCD holds at a time then cover 8 weight
-  // tiles x 4 row tiles and fetch about 256 KB of operands per K-block instead
-  // of up to 1.5 MB.
-  int nt0, m0;
+  // fastest: the work-groups an XCD holds at a time then work on the same
+  // K-blocks of neighbouring tiles and share both operands in its L2.
+  int nt0, m0, tile;
   {
     const int total = gridDim.x * gridDim.y, b = blockIdx.y * gridDim.x + blockIdx.x;
     const int q = total / 8, r = total % 8, x = b % 8, j = b / 8;
-    const int t = x * q + min(x, r) + j;
+    tile = x * q + min(x, r) + j;
     const int gm = gridDim.y % 4 == 0 ? 4 : 1;
     const int per_group = gm * gridDim.x;
-    const int mg = t / per_group, rem = t % per_group;
+    const int mg = tile / per_group, rem = tile % per_group;
     nt0 = (rem / gm) * TN;
     m0 = (mg * gm + rem % gm) * TM * 16;
   }
-  const int wn = wave % TS::GN, wm = wave / TS::GN;
-  const size_t xpart = static_cast<size_t>(Rp) * 4;  // uint4 per (K-block, part)
-
-  auto issue = [&](int kb, uint4(*dst)[64]) {
+  const int S = kSplit ? gridDim.z : 1, slice = kSplit ? blockIdx.z : 0;
+  const int kb0 = KB * slice / S, kb1 = KB * (slice + 1) / S;
+  // Loads: a running base each for weights and activations, and a 32-bit lane
+  // offset per fragment (bytes).  A wave past the last fragment repeats it.
+  const uint32_t xpart = static_cast<uint32_t>(Rp) * 64;  // bytes per (K-block, part)
+  const char* wbase = reinterpret_cast<const char*>(W) + static_cast<size_t>(nt0) * KB * 1024;
+  const char* xbase = reinterpret_cast<const char*>(X);
+  auto act_frag = [&](int i) __attribute__((always_inline)) { return min(wave + NW * (i - LW), TM * PARTS - 1); };
+  uint32_t off[L];
+#pragma unroll
+  for (int i = 0; i < L; ++i) {
+    if (i < LW) {
+      off[i] = static_cast<uint32_t>(min(nt0 + wave + NW * i, NT - 1) - nt0) * KB * 1024 + lane * 16;
+    } else {
+      const int f = act_frag(i), q = f / TM, tt = f % TM;
+      off[i] = q * xpart + min(m0 + 16 * tt, Rp - 16) * 64 + lane * 16;
+    }
+  }
+  auto issue = [&](int kb, int stage) __attribute__((always_inline)) {
+    const char* wk = wbase + static_cast<size_t>(kb) * 1024;
+    const char* xk = xbase + static_cast<size_t>(kb) * LP * xpart;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const int f = wave + NW * i;
-      const uint4* src;
-      if (f < TN) {
-        const int nt = min(nt0 + f, NT - 1);
-        src = W + (static_cast<size_t>(nt) * KB + kb) * 64 + lane;
-      } else {
-        const int a = f - TN, q = a / TM, tt = a % TM;
-        const int r0 = min(m0 + 16 * tt, Rp - 16);
-        src = X + (static_cast<size_t>(kb) * LP + q) * xpart + static_cast<size_t>(r0) * 4 + lane;
-      }
-      __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)&dst[f][0], 16, 0, 0);
+      const int f = i < LW ? wave + NW * i : TN + act_frag(i);
+      __builtin_amdgcn_global_load_lds((global_void*)((i < LW ? wk : xk) + off[i]),
+                                       (lds_void*)(lds + (stage * NFRAG + f) * 64), 16, 0, 0);
     }
   };
 
@@ -140,42 +147,45 @@ __global__ __launch_bounds__(NW * 64) void k_tile_gemm(const uint4* __restrict__
   for (int i = 0; i < WN; ++i)
 #pragma unroll
     for (int j = 0; j < WM; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  // K-block kb: its loads are the oldest in flight; the next K-block's (if
-  // any) may stay in flight.  Then the stage read at kb - 1 is free for kb + 2.
-  auto step = [&](int kb, uint4(*cur)[64], uint4(*next)[64]) {
-    if (kb + 1 < KB) {
-      wait_vmem<L>();
-    } else {
-      wait_vmem<0>();
-    }
-    lds_stage_barrier();
-    if (kb + 2 < KB) issue(kb + 2, next);
-    // Reads in the order the products use them: the weight fragments, then
-    // the activation fragments of row tile 0, 1, ...  The products of row
-    // tile j start once its reads have landed, while the later tiles' reads
-    // are still in flight.
-    u32x4_t a[WN], b[WM][PARTS];
-#pragma unroll
-    for (int i = 0; i < WN; ++i) a[i] = lds_read16(&cur[wn * WN + i][lane]);
-#pragma unroll
-    for (int j = 0; j < WM; ++j)
-#pragma unroll
-      for (int q = 0; q < PARTS; ++q) b[j][q] = lds_read16(&cur[TN + q * TM + wm * WM + j][lane]);
-    auto row_tile = [&](auto jc) {
+  const uint32_t abase = lds_address(lds + wn * WN * 64 + lane), bbase = lds_address(lds + (TN + wm * WM) * 64 + lane);
+  auto multiply = [&](int stage) __attribute__((always_inline)) {
+    // The weight fragments, then row tile by row tile the activation
+    // fragments, one row tile ahead of the products.
+    const uint32_t ab = abase + stage * (NFRAG * 1024), bb = bbase + stage * (NFRAG * 1024);
+    u32x4_t a[WN], b[2][PARTS];
+    auto read_a = [&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value;
+      a[i] = lds_read16_at<i * 1024>(ab);
+    };
+    auto read_b = [&](auto jc) __attribute__((always_inline)) {
       constexpr int j = decltype(jc)::value;
-      lds_reads_left<(WM - 1 - j) * PARTS>();
+      auto part = [&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        b[j & 1][q] = lds_read16_at<(q * TM + j) * 1024>(bb);
+      };
+      static_for<PARTS>(part);
+    };
+    read_b(std::integral_constant<int, 0>{});
+    static_for<WN>(read_a);
+    auto row_tile = [&](auto jc) __attribute__((always_inline)) {
+      constexpr int j = decltype(jc)::value;
+      if constexpr (j + 1 < WM) {
+        read_b(std::integral_constant<int, j + 1>{});
+        lds_reads_left<PARTS>();
+      } else {
+        lds_reads_left<0>();
+      }
       if constexpr (j == 0) {
 #pragma unroll
         for (int i = 0; i < WN; ++i) lds_value_ready(a[i]);
       }
 #pragma unroll
-      for (int q = 0; q < PARTS; ++q) lds_value_ready(b[j][q]);
+      for (int q = 0; q < PARTS; ++q) lds_value_ready(b[j & 1][q]);
 #pragma unroll
-      for (int i = 0; i < WN; ++i)
+      for (int q = 0; q < PARTS; ++q)
 #pragma unroll
-        for (int q = 0; q < PARTS; ++q)
-          acc[i][j] = P::mma(acc[i][j], __builtin_bit_cast(uint4, a[i]), __builtin_bit_cast(uint4, b[j][q]));
+        for (int i = 0; i < WN; ++i)
+          acc[i][j] = P::mma(acc[i][j], __builtin_bit_cast(uint4, a[i]), __builtin_bit_cast(uint4, b[j & 1][q]));
       // Keep these products ahead of the next tile's wait (the scheduler
       // would otherwise sink them below it).
       __builtin_amdgcn_sched_barrier(0);
@@ -183,12 +193,70 @@ __global__ __launch_bounds__(NW * 64) void k_tile_gemm(const uint4* __restrict__
     static_for<WM>(row_tile);
   };
 
-  issue(0, st0);
-  if (KB > 1) issue(1, st1);
-  for (int kb = 0; kb < KB; kb += 3) {
-    step(kb, st0, st2);
-    if (kb + 1 < KB) step(kb + 1, st1, st0);
-    if (kb + 2 < KB) step(kb + 2, st2, st1);
+  // K-block kb (LDS stage st): its loads are the oldest in flight; the next
+  // NST - 2 K-blocks' (if any) may stay in flight.  Then the stage read at
+  // kb - 1 is free for kb + NST - 1.
+  auto step = [&](int kb, int st, int free_st) __attribute__((always_inline)) {
+    if (kb + NST - 2 < kb1) {
+      wait_vmem<(NST - 2) * L>();
+    } else {
+      wait_vmem<0>();
+    }
+    lds_stage_barrier();
+    if (kb + NST - 1 < kb1) issue(kb + NST - 1, free_st);
+    multiply(st);
+  };
+#pragma unroll
+  for (int k = 0; k < NST - 1; ++k)
+    if (kb0 + k < kb1) issue(kb0 + k, k);
+  if constexpr (NST == 2) {
+    for (int kb = kb0; kb < kb1; kb += 2) {
+      step(kb, 0, 1);
+      if (kb + 1 < kb1) step(kb + 1, 1, 0);
+    }
+  } else {
+    for (int kb = kb0; kb < kb1; kb += 3) {
+      step(kb, 0, 2);
+      if (kb + 1 < kb1) step(kb + 1, 1, 0);
+      if (kb + 2 < kb1) step(kb + 2, 2, 1);
+    }
+  }
+  if constexpr (kSplit) {
+    constexpr size_t kWave = tile_slice_floats<TN, TM>();
+    auto slot = [&](int q) __attribute__((always_inline)) {
+      return ts.part + ((static_cast<size_t>(tile) * S + q) * NW + wave) * kWave + 2 * lane;
+    };
+    float* mine = slot(slice);
+#pragma unroll
+    for (int i = 0; i < WN; ++i)
+#pragma unroll
+      for (int j = 0; j < WM; ++j) {
+        store_coherent2(mine + (i * WM + j) * 256, acc[i][j][0], acc[i][j][1]);
+        store_coherent2(mine + (i * WM + j) * 256 + 128, acc[i][j][2], acc[i][j][3]);
+      }
+    wait_vmem<0>();  // this wave's partial sums are complete
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    int32_t* cnt = ts.cnt + tile * NW + wave;
+    int last = 0;
+    if (lane == 0) last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1;
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    if (lane == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int q = 0; q < S; ++q) {
+      const float* p = slot(q);
+#pragma unroll
+      for (int i = 0; i < WN; ++i)
+#pragma unroll
+        for (int j = 0; j < WM; ++j) {
+          const float2 lo = load_coherent2(p + (i * WM + j) * 256), hi = load_coherent2(p + (i * WM + j) * 256 + 128);
+          const f32x4_t v = {lo.x, lo.y, hi.x, hi.y};
+          if (q == 0) {
+            acc[i][j] = v;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][e] += v[e];
+          }
+        }
+    }
   }
 #pragma unroll
   for (int i = 0; i < WN; ++i) {

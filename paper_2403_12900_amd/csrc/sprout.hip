@@ -37,6 +37,7 @@
 #include "panel_launch.h"
 #include "prefill_kernels.h"
 #include "step_kernels.h"
+#include "tile_launch.h"
 #include "wgen_kernels.h"
 
 using namespace sprk;
@@ -546,37 +547,11 @@ void launch_attn_prefill(spr_model* m, int layer, const PrefillChunk& ch, const 
                                                                        qscale);
 }
 
-// Tile shape of a prefill projection: 256 x 256 eight-wave work-groups when
-// that gives at least one per CU (256; measured 3% faster on 7B-shape 4096-row
-// chunks than requiring 512), else 128 x 128 when that gives at least 512,
-// else 64 features x 128 rows, else 64 x 64.
-// Three-part activations (QKV) take 256 features x 128 rows instead of 256 x
-// 256: the larger tile's three LDS stages would need 192 KiB.
-// LP: parts per K-block of the activation record X (P::parts used).
+// Projection of a prefill chunk's Rp padded rows (LP: parts per K-block of X).
 template <class P, class Epi, int LP = P::parts>
-void launch_tile_gemm(hipStream_t st, const char* W, const char* X, int NT, int KB, int Rp, const Epi& e) {
-  const uint4* w = reinterpret_cast<const uint4*>(W);
-  const uint4* x = reinterpret_cast<const uint4*>(X);
-  const int mt = Rp / 128;
-  if constexpr (P::parts == 3) {
-    if (ceil_div(NT, 16) * mt >= 256) {
-      k_tile_gemm<P, 16, 8, Epi, 8, LP><<<dim3(ceil_div(NT, 16), mt), 512, 0, st>>>(w, x, NT, KB, Rp, e);
-      return;
-    }
-  } else {
-    if (ceil_div(NT, 16) * ceil_div(Rp, 256) >= 256) {
-      k_tile_gemm<P, 16, 16, Epi, 8, LP><<<dim3(ceil_div(NT, 16), ceil_div(Rp, 256)), 512, 0, st>>>(w, x, NT, KB, Rp,
-                                                                                                    e);
-      return;
-    }
-  }
-  if (ceil_div(NT, 8) * mt >= 512) {
-    k_tile_gemm<P, 8, 8, Epi, 4, LP><<<dim3(ceil_div(NT, 8), mt), 256, 0, st>>>(w, x, NT, KB, Rp, e);
-  } else if (ceil_div(NT, 4) * mt >= 512) {
-    k_tile_gemm<P, 4, 8, Epi, 4, LP><<<dim3(ceil_div(NT, 4), mt), 256, 0, st>>>(w, x, NT, KB, Rp, e);
-  } else {
-    k_tile_gemm<P, 4, 4, Epi, 4, LP><<<dim3(ceil_div(NT, 4), Rp / 64), 256, 0, st>>>(w, x, NT, KB, Rp, e);
-  }
+void tile_gemm(hipStream_t st, const char* W, const char* X, int NT, int KB, int Rp, const Epi& e,
+               const SplitRoom& room) {
+  launch_tile_gemm<P, LP>(st, NT, reinterpret_cast<const uint4*>(W), reinterpret_cast<const uint4*>(X), KB, Rp, e, room);
 }
 
 template <class P, class KP>
@@ -586,8 +561,9 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   using E = typename P::elem;
   const int C = ch.C;
   // A bf16 chunk that a decode pass could hold runs its projections as a
-  // decode pass does: they are still bound by the weight stream (128 rows of
-  // the 7B shape, a layer's projections: 205 us against 345).
+  // decode pass does: they are still bound by the weight stream, and the panel
+  // kernel needs no row scales beforehand (8 layers of the 7B shape, 65 / 128
+  // rows: 1.65 / 1.82 ms against 1.77 / 1.85 ms tiled).
   const bool small = P::parts >= 2 && C <= kRows;
   const int Rp = small ? 16 * row_tiles(C) : 128 * ceil_div(C, 128);
   const ActRec rec = act_rec(Rp);
@@ -610,7 +586,7 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
         continue;
       }
     }
-    k_row_rscale<<<ceil_div(C, 4), 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
+    k_row_rscale<<<C, 256, 0, m->st>>>(p.x(), p.rs(), d.d, d.eps);
     {
       EpiQKVRows<P, KP> e{};
       e.M = C;
@@ -630,12 +606,12 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
         // Query tiles take hi + mid of the three-part record (and the larger
         // two-part tiles), key and value tiles all three parts.
         const int q_tiles = d.H * d.hd / 16;
-        launch_tile_gemm<P, EpiQKVRows<P, KP>, 3>(m->st, p.wqkv(l), p.act(0), q_tiles, d.kb_d, Rp, e);
+        tile_gemm<P, EpiQKVRows<P, KP>, 3>(m->st, p.wqkv(l), p.act(0), q_tiles, d.kb_d, Rp, e, room);
         e.nt_base = q_tiles;
         const char* wkv = p.wqkv(l) + static_cast<size_t>(q_tiles) * d.kb_d * 64 * sizeof(uint4);
-        launch_tile_gemm<QKVIn<P>>(m->st, wkv, p.act(0), d.nt_qkv - q_tiles, d.kb_d, Rp, e);
+        tile_gemm<QKVIn<P>>(m->st, wkv, p.act(0), d.nt_qkv - q_tiles, d.kb_d, Rp, e, room);
       } else {
-        launch_tile_gemm<QKVIn<P>>(m->st, p.wqkv(l), p.act(0), d.nt_qkv, d.kb_d, Rp, e);
+        tile_gemm<QKVIn<P>>(m->st, p.wqkv(l), p.act(0), d.nt_qkv, d.kb_d, Rp, e, room);
       }
     }
     if (d.hd == 128) {
@@ -645,16 +621,16 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
     }
     {
       EpiResidRows<P> e{C, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      launch_tile_gemm<P>(m->st, p.wo(l), p.act(1), d.nt_o, d.kb_o, Rp, e);
+      tile_gemm<P>(m->st, p.wo(l), p.act(1), d.nt_o, d.kb_o, Rp, e, room);
     }
-    k_row_rscale<<<ceil_div(C, 4), 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
+    k_row_rscale<<<C, 256, 0, m->st>>>(p.x(), p.rs(), d.d, d.eps);
     {
       EpiSwiGLURows<P> e{C, rec, p.rs(), reinterpret_cast<E*>(p.act(1))};
-      launch_tile_gemm<P>(m->st, p.w13(l), p.act(0), d.nt_13, d.kb_d, Rp, e);
+      tile_gemm<P>(m->st, p.w13(l), p.act(0), d.nt_13, d.kb_d, Rp, e, room);
     }
     {  // the new residual is the next layer's QKV input (the prompt's last rows reach the LM head from x)
       EpiResidRows<QKVIn<P>> e{C, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      launch_tile_gemm<P>(m->st, p.w2(l), p.act(1), d.nt_2, d.kb_f, Rp, e);
+      tile_gemm<P>(m->st, p.w2(l), p.act(1), d.nt_2, d.kb_f, Rp, e, room);
     }
     SPR_LAUNCHED(m, "prefill layer");
   }

@@ -1,5 +1,5 @@
-// Per-step kernels around the layer stack: token embedding and the final
-// greedy token (lowest index among equal maxima).
+// Per-step kernels around the layer stack: token embedding, the final greedy
+// token (lowest index among equal maxima), and a prefill chunk's row scales.
 #pragma once
 
 #include "gemm_kernels.h"
@@ -102,6 +102,25 @@ __global__ __launch_bounds__(256) void k_argmax_final(ArgmaxArgs a) {
     a.tok_dev[a.slot[b]] = idx;
     if (a.hist != nullptr && a.hist_idx[b] >= 0) a.hist[a.hist_idx[b]] = idx;
   }
+}
+
+// RMSNorm scale of each row (unit gains): rs[b] = 1 / sqrt(mean(x_b^2) + eps).
+// One work-group per row: a few hundred rows are bound by the latency of a
+// row's loads, which four waves issue at once (128 rows of 4096: 5.9 us with a
+// wave per row).
+__global__ __launch_bounds__(256) void k_row_rscale(const float* __restrict__ x, float* rs, int d, float eps) {
+  const int b = blockIdx.x;
+  const float* xr = x + static_cast<size_t>(b) * d;
+  float s = 0.f;
+  for (int k = 4 * threadIdx.x; k < d; k += 1024) {
+    const float4 v = *reinterpret_cast<const float4*>(xr + k);
+    s = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, s))));
+  }
+  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  __shared__ float part[4];
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) rs[b] = rsqrtf((part[0] + part[1] + part[2] + part[3]) / static_cast<float>(d) + eps);
 }
 
 // out[0 .. n) = 0.

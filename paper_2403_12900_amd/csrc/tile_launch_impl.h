@@ -1,0 +1,95 @@
+// Shapes of the tiled projection and the rule that picks one (see
+// tile_launch.h).
+#pragma once
+
+#include <iterator>
+#include <utility>
+
+#include "tile_launch.h"
+
+namespace sprk {
+
+inline int tile_div(int a, int b) { return (a + b - 1) / b; }
+
+// A shape of k_tile_gemm and its measured times in microseconds (MI355X, two
+// and three activation parts): a K-block of a tile when its work-group is
+// alone on its CU, and when others share the CU (per tile); the start and end
+// of a tile; the publication of a split tile, and of each further slice.
+struct TileShape {
+  int tn, tm, nst;
+  struct Cost {
+    double alone, shared, tile, split, slice;
+  } two, three;
+};
+constexpr TileShape kTileShapes[] = {
+    {16, 8, 2, {0.773, 0.720, 6.3, 15.9, 0.66}, {1.148, 1.079, 0.0, 20.3, 0.99}},
+    {8, 8, 2, {0.513, 0.403, 2.3, 12.2, 0.15}, {0.687, 0.606, 0.0, 14.8, 0.33}},
+    {8, 4, 2, {0.467, 0.223, 0.4, 8.0, 0.24}, {0.488, 0.299, 0.0, 8.7, 0.30}},
+    {4, 4, 3, {0.229, 0.146, 0.0, 6.1, 0.09}, {0.308, 0.182, 1.3, 5.3, 0.00}},
+};
+
+// The pick: the least estimated time.  The busiest CU's tiles (halfway between
+// the whole number and the mean, since a CU left with fewer runs them faster)
+// are multiplied one after another at the shared rate, but a tile alone is
+// bound by its own latency; fitted to 260 timings of the 7B, 13B and 70B
+// projections at 256 to 4096 rows, its choices are 1.3% slower than the
+// fastest on average.
+struct TilePick {
+  int shape = 0, slices = 1;
+};
+inline TilePick tile_pick(int NT, int KB, int Rp, int parts, const SplitRoom& room) {
+  constexpr int kCUs = 256, kMaxSlices = 8;
+  TilePick best;
+  double best_us = -1;
+  for (int i = 0; i < static_cast<int>(std::size(kTileShapes)); ++i) {
+    const TileShape& s = kTileShapes[i];
+    const TileShape::Cost& c = parts == 3 ? s.three : s.two;
+    const int64_t tiles = int64_t{tile_div(NT, s.tn)} * tile_div(Rp / 16, s.tm);
+    const size_t slice_floats = static_cast<size_t>(s.tn) * s.tm * 256;
+    for (int S = 1; S <= kMaxSlices && S <= KB; ++S) {
+      if (S > 1 && (room.part == nullptr || tiles * kTileWaves > room.n_cnt ||
+                    static_cast<size_t>(tiles) * S * slice_floats > room.part_floats))
+        break;
+      const double mean = static_cast<double>(tiles) * S / kCUs;
+      const double k = 0.5 * static_cast<double>((tiles * S + kCUs - 1) / kCUs) + 0.5 * (mean > 1 ? mean : 1);
+      const double kb_us = c.alone > k * c.shared ? c.alone : k * c.shared;
+      double us = tile_div(KB, S) * kb_us + k * c.tile;
+      if (S > 1) us += c.split + c.slice * S * static_cast<double>((tiles * S + kCUs - 1) / kCUs);
+      if (best_us < 0 || us < best_us) {
+        best = TilePick{i, S};
+        best_us = us;
+      }
+    }
+  }
+  return best;
+}
+
+template <class P, int LP, size_t I, class Epi>
+void launch_tile_shape(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, int Rp, const Epi& epi,
+                       const SplitRoom& room, int S) {
+  constexpr TileShape s = kTileShapes[I];
+  const dim3 grid(tile_div(NT, s.tn), tile_div(Rp / 16, s.tm), S);
+  const TileSplit ts{room.part, room.cnt};
+  if (S == 1) {
+    k_tile_gemm<P, s.tn, s.tm, s.nst, false, Epi, LP><<<grid, kTileWaves * 64, 0, st>>>(w, x, NT, KB, Rp, ts, epi);
+  } else {
+    k_tile_gemm<P, s.tn, s.tm, s.nst, true, Epi, LP><<<grid, kTileWaves * 64, 0, st>>>(w, x, NT, KB, Rp, ts, epi);
+  }
+}
+
+template <class P, int LP, class Epi, size_t... I>
+void launch_tile_pick(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, int Rp, const Epi& epi,
+                      const SplitRoom& room, std::index_sequence<I...>) {
+  const TilePick pick = tile_pick(NT, KB, Rp, P::parts, room);
+  (void)((static_cast<int>(I) == pick.shape &&
+          (launch_tile_shape<P, LP, I>(st, NT, w, x, KB, Rp, epi, room, pick.slices), true)) ||
+         ...);
+}
+
+template <class P, int LP, class Epi>
+void launch_tile_gemm(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, int Rp, const Epi& epi,
+                      const SplitRoom& room) {
+  launch_tile_pick<P, LP>(st, NT, w, x, KB, Rp, epi, room, std::make_index_sequence<std::size(kTileShapes)>{});
+}
+
+}  // namespace sprk
