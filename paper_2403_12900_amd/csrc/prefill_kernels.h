@@ -391,8 +391,14 @@ __global__ __launch_bounds__(256) void k_attn_prefill(const float* __restrict__ 
   constexpr int PER = KVU / 256;                     // uint4 each thread stages per block
   static_assert(KVU % 256 == 0, "a block's K and V tiles split evenly over the work-group");
   __shared__ uint4 skv[2][KVU];
-  const PrefillTile tile = tiles[blockIdx.x];
-  const int hq = blockIdx.y, kvh = hq / (H / Hkv);
+  // Heads fastest, so that every XCD takes all of the tiles (their lengths
+  // differ), and the tiles that end their prompts, whose walks are longest,
+  // first.  Where H is a multiple of 8, an XCD takes H / 8 consecutive heads:
+  // the heads of a KV group share its L2.  (1500 positions of the 70B shape, 4
+  // layers: 17.5 ms against 18.3 ms tiles fastest, where the XCD of the last
+  // tiles walked 1.3 times the mean.)
+  const PrefillTile tile = tiles[gridDim.y - 1 - blockIdx.y];
+  const int hx = blockIdx.x, hq = H % 8 == 0 ? (hx % 8) * (H / 8) + hx / 8 : hx, kvh = hq / (H / Hkv);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;

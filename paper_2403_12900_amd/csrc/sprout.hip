@@ -308,10 +308,11 @@ spr_status launch_attention(spr_model* m, const AttnArgs& a) {
   return SPR_OK;
 }
 
-// Attention arguments of one layer over rs (kv splits of bpw blocks per wave).
+// Attention arguments of one layer over rs (kv splits of bpw blocks per wave;
+// order: its rows in launch order; rounds: more work-groups than stay resident).
 template <class P, class KP>
-AttnArgs attention_args(spr_model* m, int l, const RowSet& rs, const RowSlotPos& sp, const ActRec& rec, int bpw, void* act,
-                        const DecodeScratch& sc) {
+AttnArgs attention_args(spr_model* m, int l, const RowSet& rs, const ActRec& rec, int bpw, const uint8_t* order,
+                        bool rounds, void* act, const DecodeScratch& sc) {
   const spr::Dims& d = m->d;
   Ptrs p{m->ws, &m->lay};
   AttnArgs a{};
@@ -330,9 +331,14 @@ AttnArgs attention_args(spr_model* m, int l, const RowSet& rs, const RowSlotPos&
   a.bpw = bpw;
   a.rec = rec;
   a.qscale = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(d.hd)));
-  a.rows = sp;
   a.split_start[0] = 0;
-  for (int r = 0; r < rs.n; ++r) a.split_start[r + 1] = a.split_start[r] + ceil_div((rs.pos[r] + 1 + 15) / 16, 4 * bpw);
+  for (int r = 0; r < rs.n; ++r) {
+    a.rows.slot[r] = rs.slot[order[r]];
+    a.rows.pos[r] = rs.pos[order[r]];
+    a.row[r] = order[r];
+    a.split_start[r + 1] = a.split_start[r] + ceil_div((rs.pos[order[r]] + 1 + 15) / 16, 4 * bpw);
+  }
+  a.even = rounds;
   return a;
 }
 
@@ -456,11 +462,16 @@ spr_status forward(spr_model* m, const RowSet& rs, const int32_t* tok_in, int32_
   for (int r = 0; r < n; ++r)
     while (ceil_div((rs.pos[r] + 1 + 15) / 16, 4 * bpw) > kMergeChunk) ++bpw;
 
+  uint8_t order[kRows];
+  for (int r = 0; r < n; ++r) order[r] = static_cast<uint8_t>(r);
+  const bool rounds = count_splits(bpw) * d.Hkv > m->attn_slots;  // more work-groups than stay resident
+  if (rounds) std::stable_sort(order, order + n, [&](uint8_t i, uint8_t j) { return rs.pos[i] > rs.pos[j]; });
+
   const SplitRoom room = split_room(sc);
   spr_status st;
   for (int l = 0; l < d.L; ++l) {
     if ((st = qkv_projection<P, KP>(m, l, n, sp, room)) != SPR_OK) return st;
-    const AttnArgs a = attention_args<P, KP>(m, l, rs, sp, rec, bpw, p.act(1), sc);
+    const AttnArgs a = attention_args<P, KP>(m, l, rs, rec, bpw, order, rounds, p.act(1), sc);
     st = d.hd == 128 ? launch_attention<P, KP, 128>(m, a) : launch_attention<P, KP, 64>(m, a);
     if (st != SPR_OK) return st;
     if ((st = mlp_projections<P>(m, l, n, l + 1 < d.L, room)) != SPR_OK) return st;
@@ -542,7 +553,7 @@ void launch_attn_prefill(spr_model* m, int layer, const PrefillChunk& ch, const 
   const spr::Dims& d = m->d;
   Ptrs p{m->ws, &m->lay};
   const float qscale = static_cast<float>(1.4426950408889634 / std::sqrt(static_cast<double>(d.hd)));
-  k_attn_prefill<KP, P, HD><<<dim3(ch.n_tiles, d.H), 256, 0, m->st>>>(p.q(), p.kc(layer), p.vc(layer), p.bt(),
+  k_attn_prefill<KP, P, HD><<<dim3(d.H, ch.n_tiles), 256, 0, m->st>>>(p.q(), p.kc(layer), p.vc(layer), p.bt(),
                                                                        p.ptile(), p.act(1), d.H, d.Hkv, d.mb, rec,
                                                                        qscale);
 }
