@@ -33,6 +33,25 @@ __device__ __forceinline__ float2 load_coherent2(const float* p) {
   return make_float2(__uint_as_float(static_cast<uint32_t>(v)), __uint_as_float(static_cast<uint32_t>(v >> 32)));
 }
 
+// The same for 16 bytes: buffer accesses with the sc1 (agent-coherent) cache
+// policy that the 8-byte atomics compile to, relative to a wave-uniform base.
+// Relaxed, and ordered against atomics only by the caller's vmcnt wait and
+// signal fence.
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+struct CoherentBuffer {
+  __amdgpu_buffer_rsrc_t rsrc;
+  static constexpr int kSc1 = 16;
+  // base: wave-uniform; accesses up to `bytes` past it.
+  __device__ __forceinline__ CoherentBuffer(float* base, uint32_t bytes)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000)) {}
+  __device__ __forceinline__ void store4(uint32_t byte, const f32x4_t& v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4_t, v), rsrc, byte, 0, kSc1);
+  }
+  __device__ __forceinline__ f32x4_t load4(uint32_t byte) const {
+    return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, byte, 0, kSc1));
+  }
+};
+
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));  // round to nearest even
 }

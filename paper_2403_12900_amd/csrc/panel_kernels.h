@@ -40,15 +40,15 @@ namespace sprk {
 // groups go to the XCDs round robin) and each L2 holds only its slices'
 // activations.
 struct SplitK {
-  float* part;    // [group][wave][slice][pair][64 lanes][2] floats
+  float* part;    // [group][wave][slice][fragment][64 lanes][4] floats
   int32_t* cnt;   // [group][wave] arrived slices; zero between launches
 };
 
-// Pairs of floats each lane publishes per slice: accumulators, then sums of
-// squares.
+// Fragments of four floats a lane publishes per slice: accumulators, then sums
+// of squares.
 template <int JT, int RT, bool kNorm>
-struct SplitKPairs {
-  static constexpr int value = (RT * JT * 4 + (kNorm ? JT : 0) + 1) / 2;
+struct SplitKQuads {
+  static constexpr int value = RT * JT + (kNorm ? (JT + 3) / 4 : 0);
 };
 
 template <int RT, int UC>
@@ -292,22 +292,23 @@ __device__ __forceinline__ void panel_tiles(const uint4* W, const uint4* X, int 
   }
 
   if (S > 1) {
-    constexpr int NP = SplitKPairs<JT, RT, Epi::kNorm>::value;
-    constexpr int NA = RT * JT * 2;  // pairs of accumulators; then sums of squares
-    auto pair = [&](int i) __attribute__((always_inline)) {
-      if (i < NA) {
-        const f32x4_t& a = acc[i / (2 * JT)][(i / 2) % JT];
-        return i & 1 ? make_float2(a[2], a[3]) : make_float2(a[0], a[1]);
-      }
-      const int j = 2 * (i - NA);
-      return make_float2(ssq[j], j + 1 < JT ? ssq[j + 1] : 0.f);
+    // Fragments of four floats a lane: accumulators, then sums of squares.
+    constexpr int NA = RT * JT, NQ = SplitKQuads<JT, RT, Epi::kNorm>::value;
+    const int g = __builtin_amdgcn_readfirstlane((nt0 / (NW * RT)) * NW + wave);
+    const CoherentBuffer buf(sk.part + static_cast<size_t>(g) * S * NQ * 256, static_cast<uint32_t>(S) * NQ * 1024);
+    auto at = [&](int q, int i) __attribute__((always_inline)) {
+      return static_cast<uint32_t>((q * NQ + i) * 1024 + lane * 16);
     };
-    const int g = (nt0 / (NW * RT)) * NW + wave;
-    float* base = sk.part + static_cast<size_t>(g) * S * NP * 128 + 2 * lane;
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const float2 v = pair(i);
-      store_coherent2(base + (static_cast<size_t>(slice) * NP + i) * 128, v.x, v.y);
+    for (int i = 0; i < NA; ++i) buf.store4(at(slice, i), acc[i / JT][i % JT]);
+    if constexpr (Epi::kNorm) {
+#pragma unroll
+      for (int i = 0; i < NQ - NA; ++i) {
+        f32x4_t v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = 4 * i + e < JT ? ssq[4 * i + e] : 0.f;
+        buf.store4(at(slice, NA + i), v);
+      }
     }
     wait_vmem<0>();  // this slice's partial stores are complete
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -315,29 +316,25 @@ __device__ __forceinline__ void panel_tiles(const uint4* W, const uint4* X, int 
     if (lane == 0) last = __hip_atomic_fetch_add(sk.cnt + g, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1;
     if (!__builtin_amdgcn_readfirstlane(last)) return;
     if (lane == 0) __hip_atomic_store(sk.cnt + g, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // Sum in slice order; all of a slice's loads are in flight at once, the
-    // next slice's while one is added.
-    float2 sum[NP], nx[NP];
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    // Sum in slice order; all of a slice's loads are in flight at once.
+    f32x4_t sum[NQ];
 #pragma unroll
-    for (int i = 0; i < NP; ++i) sum[i] = load_coherent2(base + static_cast<size_t>(i) * 128);
+    for (int i = 0; i < NQ; ++i) sum[i] = buf.load4(at(0, i));
     for (int q = 1; q < S; ++q) {
+      f32x4_t nx[NQ];
 #pragma unroll
-      for (int i = 0; i < NP; ++i) nx[i] = load_coherent2(base + (static_cast<size_t>(q) * NP + i) * 128);
+      for (int i = 0; i < NQ; ++i) nx[i] = buf.load4(at(q, i));
 #pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        sum[i].x += nx[i].x;
-        sum[i].y += nx[i].y;
-      }
+      for (int i = 0; i < NQ; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[i][e] += nx[i][e];
     }
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      f32x4_t& a = acc[i / (2 * JT)][(i / 2) % JT];
-      a[2 * (i & 1)] = sum[i].x;
-      a[2 * (i & 1) + 1] = sum[i].y;
-    }
+    for (int i = 0; i < NA; ++i) acc[i / JT][i % JT] = sum[i];
     if constexpr (Epi::kNorm) {
 #pragma unroll
-      for (int j = 0; j < JT; ++j) ssq[j] = j & 1 ? sum[NA + j / 2].y : sum[NA + j / 2].x;
+      for (int j = 0; j < JT; ++j) ssq[j] = sum[NA + j / 4][j % 4];
     }
   }
 #pragma unroll

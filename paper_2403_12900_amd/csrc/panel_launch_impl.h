@@ -71,9 +71,9 @@ inline PanelPick panel_pick(const PanelShape* sh, int n_shapes, int NT, int KB, 
   double best_us = 0;
   for (int i = 0; i < n_shapes; ++i) {
     const int T = sh[i].nw * sh[i].rt, groups = panel_div(NT, T), chunks = panel_div(KB, sh[i].uc);
-    const size_t pairs = (sh[i].rt * JT * 4 + (norm ? JT : 0) + 1) / 2;
+    const size_t quads = sh[i].rt * JT + (norm ? (JT + 3) / 4 : 0);
     for (int S = 1; S <= kMaxSlices && S <= chunks; ++S) {
-      if (S > 1 && static_cast<size_t>(groups) * sh[i].nw * S * pairs * 128 * sizeof(float) > room) break;
+      if (S > 1 && static_cast<size_t>(groups) * sh[i].nw * S * quads * 256 * sizeof(float) > room) break;
       const double chain = 1.0 * panel_div(groups * S, kCUs) * panel_div(KB, S) *
                            (0.012 * T + (0.0097 + 0.003 * sh[i].nw) * JT * parts);
       const double hbm = 1.62e-4 * NT * KB;

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(64) void k_embed_rows(const typename P::elem* __res
 // the work-groups of an XCD then read different K-blocks and share nothing in
 // its L2.
 struct TileSplit {
-  float* part;    // [tile][slice][wave][tile fragment][2][64 lanes][2] floats
+  float* part;    // [tile][slice][wave][tile fragment][64 lanes][4] floats
   int32_t* cnt;   // [tile][wave] arrived slices; zero between launches
 };
 constexpr int kTileWaves = 4;
@@ -222,18 +222,13 @@ __global__ __launch_bounds__(256, 2) void k_tile_gemm(const uint4* W, const uint
     }
   }
   if constexpr (kSplit) {
-    constexpr size_t kWave = tile_slice_floats<TN, TM>();
-    auto slot = [&](int q) __attribute__((always_inline)) {
-      return ts.part + ((static_cast<size_t>(tile) * S + q) * NW + wave) * kWave + 2 * lane;
+    constexpr uint32_t kWave = tile_slice_floats<TN, TM>() * sizeof(float);  // bytes of a wave's slice
+    const CoherentBuffer buf(ts.part + static_cast<size_t>(tile) * S * NW * (kWave / 4), S * NW * kWave);
+    auto at = [&](int q, int i) __attribute__((always_inline)) {
+      return static_cast<uint32_t>((q * NW + wave) * kWave + i * 1024 + lane * 16);
     };
-    float* mine = slot(slice);
 #pragma unroll
-    for (int i = 0; i < WN; ++i)
-#pragma unroll
-      for (int j = 0; j < WM; ++j) {
-        store_coherent2(mine + (i * WM + j) * 256, acc[i][j][0], acc[i][j][1]);
-        store_coherent2(mine + (i * WM + j) * 256 + 128, acc[i][j][2], acc[i][j][3]);
-      }
+    for (int i = 0; i < WN * WM; ++i) buf.store4(at(slice, i), acc[i / WM][i % WM]);
     wait_vmem<0>();  // this wave's partial sums are complete
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     int32_t* cnt = ts.cnt + tile * NW + wave;
@@ -241,21 +236,18 @@ __global__ __launch_bounds__(256, 2) void k_tile_gemm(const uint4* W, const uint
     if (lane == 0) last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == S - 1;
     if (!__builtin_amdgcn_readfirstlane(last)) return;
     if (lane == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
     for (int q = 0; q < S; ++q) {
-      const float* p = slot(q);
 #pragma unroll
-      for (int i = 0; i < WN; ++i)
+      for (int i = 0; i < WN * WM; ++i) {
+        const f32x4_t v = buf.load4(at(q, i));
+        if (q == 0) {
+          acc[i / WM][i % WM] = v;
+        } else {
 #pragma unroll
-        for (int j = 0; j < WM; ++j) {
-          const float2 lo = load_coherent2(p + (i * WM + j) * 256), hi = load_coherent2(p + (i * WM + j) * 256 + 128);
-          const f32x4_t v = {lo.x, lo.y, hi.x, hi.y};
-          if (q == 0) {
-            acc[i][j] = v;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][e] += v[e];
-          }
+          for (int e = 0; e < 4; ++e) acc[i / WM][i % WM][e] += v[e];
         }
+      }
     }
   }
 #pragma unroll
