@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256, 2) void k_tile_gemm(const uint4* W, const uint
   auto step = [&](int kb, int st, int free_st) __attribute__((always_inline)) {
     if (kb + NST - 2 < kb1) {
       wait_vmem<(NST - 2) * L>();
-    } else {
+    } else {  // the last K-blocks: fewer loads in flight
       wait_vmem<0>();
     }
     lds_stage_barrier();
@@ -209,17 +209,12 @@ __global__ __launch_bounds__(256, 2) void k_tile_gemm(const uint4* W, const uint
 #pragma unroll
   for (int k = 0; k < NST - 1; ++k)
     if (kb0 + k < kb1) issue(kb0 + k, k);
-  if constexpr (NST == 2) {
-    for (int kb = kb0; kb < kb1; kb += 2) {
-      step(kb, 0, 1);
-      if (kb + 1 < kb1) step(kb + 1, 1, 0);
-    }
-  } else {
-    for (int kb = kb0; kb < kb1; kb += 3) {
-      step(kb, 0, 2);
-      if (kb + 1 < kb1) step(kb + 1, 1, 0);
-      if (kb + 2 < kb1) step(kb + 2, 2, 1);
-    }
+  for (int kb = kb0; kb < kb1; kb += NST) {
+    auto one = [&](auto sc) __attribute__((always_inline)) {
+      constexpr int st = decltype(sc)::value;
+      if (kb + st < kb1) step(kb + st, st, (st + NST - 1) % NST);
+    };
+    static_for<NST>(one);
   }
   if constexpr (kSplit) {
     constexpr uint32_t kWave = tile_slice_floats<TN, TM>() * sizeof(float);  // bytes of a wave's slice

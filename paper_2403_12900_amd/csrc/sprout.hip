@@ -573,8 +573,9 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   const int C = ch.C;
   // A bf16 chunk that a decode pass could hold runs its projections as a
   // decode pass does: they are still bound by the weight stream, and the panel
-  // kernel needs no row scales beforehand (8 layers of the 7B shape, 65 / 128
-  // rows: 1.65 / 1.82 ms against 1.77 / 1.85 ms tiled).
+  // kernel needs no row scales beforehand (panel / tiled: 8 layers of the 7B
+  // shape, 96 rows 1.50 / 1.83 ms, 128 rows 1.82 / 1.87 ms; 8 layers of 13B,
+  // 96 rows 1.98 / 2.39 ms, 128 rows 2.58 / 2.43 ms).
   const bool small = P::parts >= 2 && C <= kRows;
   const int Rp = small ? 16 * row_tiles(C) : 128 * ceil_div(C, 128);
   const ActRec rec = act_rec(Rp);

@@ -2,6 +2,7 @@
 // tile_launch.h).
 #pragma once
 
+#include <cmath>
 #include <iterator>
 #include <utility>
 
@@ -14,7 +15,8 @@ inline int tile_div(int a, int b) { return (a + b - 1) / b; }
 // A shape of k_tile_gemm and its measured times in microseconds (MI355X, two
 // and three activation parts): a K-block of a tile when its work-group is
 // alone on its CU, and when others share the CU (per tile); the start and end
-// of a tile; the publication of a split tile, and of each further slice.
+// of a tile; the publication of a split tile, and of each further slice.  The
+// last shape's four stages cover HBM latency where tiles are few.
 struct TileShape {
   int tn, tm, nst;
   struct Cost {
@@ -22,18 +24,18 @@ struct TileShape {
   } two, three;
 };
 constexpr TileShape kTileShapes[] = {
-    {16, 8, 2, {0.773, 0.720, 6.3, 15.9, 0.66}, {1.148, 1.079, 0.0, 20.3, 0.99}},
-    {8, 8, 2, {0.513, 0.403, 2.3, 12.2, 0.15}, {0.687, 0.606, 0.0, 14.8, 0.33}},
-    {8, 4, 2, {0.467, 0.223, 0.4, 8.0, 0.24}, {0.488, 0.299, 0.0, 8.7, 0.30}},
-    {4, 4, 3, {0.229, 0.146, 0.0, 6.1, 0.09}, {0.308, 0.182, 1.3, 5.3, 0.00}},
+    {16, 8, 2, {0.827, 0.743, 1.8, 14.1, 1.26}, {1.067, 1.057, 0.0, 15.4, 1.07}},
+    {8, 8, 2, {0.692, 0.420, 0.0, 11.5, 0.66}, {0.756, 0.595, 0.0, 12.4, 0.54}},
+    {8, 4, 2, {0.618, 0.257, 0.8, 7.9, 0.28}, {0.627, 0.275, 3.0, 7.0, 0.06}},
+    {8, 4, 4, {0.289, 0.250, 1.0, 8.3, 0.21}, {0.386, 0.307, 1.7, 8.1, 0.13}},
 };
 
 // The pick: the least estimated time.  The busiest CU's tiles (halfway between
 // the whole number and the mean, since a CU left with fewer runs them faster)
 // are multiplied one after another at the shared rate, but a tile alone is
-// bound by its own latency; fitted to 260 timings of the 7B, 13B and 70B
-// projections at 256 to 4096 rows, its choices are 1.3% slower than the
-// fastest on average.
+// bound by its own latency; the HBM time of the weights adds in quadrature.
+// Fitted to 900 timings of the 7B, 13B and 70B projections at 128 to 4096 rows
+// with weights from HBM; its choices are 2% slower than the fastest on average.
 struct TilePick {
   int shape = 0, slices = 1;
 };
@@ -53,7 +55,8 @@ inline TilePick tile_pick(int NT, int KB, int Rp, int parts, const SplitRoom& ro
       const double mean = static_cast<double>(tiles) * S / kCUs;
       const double k = 0.5 * static_cast<double>((tiles * S + kCUs - 1) / kCUs) + 0.5 * (mean > 1 ? mean : 1);
       const double kb_us = c.alone > k * c.shared ? c.alone : k * c.shared;
-      double us = tile_div(KB, S) * kb_us + k * c.tile;
+      const double chain = tile_div(KB, S) * kb_us + k * c.tile, hbm = 1.62e-4 * NT * KB;
+      double us = std::sqrt(chain * chain + hbm * hbm);
       if (S > 1) us += c.split + c.slice * S * static_cast<double>((tiles * S + kCUs - 1) / kCUs);
       if (best_us < 0 || us < best_us) {
         best = TilePick{i, S};
