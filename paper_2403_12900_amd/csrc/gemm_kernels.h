@@ -348,6 +348,19 @@ __device__ __forceinline__ void store_act4(typename P::elem* act, const ActRec& 
   act_store<P, 4>(act, rec, b, n0, v);
 }
 
+// store_act4 of the residual (d features): where d ends inside a K-block (16
+// of 32 elements), the lanes of its last 16 features also clear the other 16.
+// The matching weights are zero, but the Gram products of the norms would
+// count what an earlier record left there.
+template <class P>
+__device__ __forceinline__ void store_resid4(typename P::elem* act, const ActRec& rec, int b, int n0, int d,
+                                             const float4& v) {
+  store_act4<P>(act, rec, b, n0, v.x, v.y, v.z, v.w);
+  if constexpr (P::kblk == 32) {
+    if (d % 32 != 0 && n0 >= d - 16) store_act4<P>(act, rec, b, n0 + 16, 0.f, 0.f, 0.f, 0.f);
+  }
+}
+
 // QKV projection -> RMSNorm scale -> RoPE on q and k -> q to the attention
 // input, k and v appended to the paged KV cache at the row's position.
 // Per (block, KV head) the K tile is 16 positions x head_dim in MFMA fragment
@@ -479,7 +492,7 @@ struct EpiResid {
       xv.z += acc[j][2];
       xv.w += acc[j][3];
       *xp = xv;
-      store_act4<P>(act, rec, b, n0, xv.x, xv.y, xv.z, xv.w);
+      store_resid4<P>(act, rec, b, n0, d, xv);
     }
   }
 };

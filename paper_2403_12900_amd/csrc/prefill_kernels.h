@@ -39,7 +39,7 @@ __global__ __launch_bounds__(64) void k_embed_rows(const typename P::elem* __res
   const typename P::elem* e = emb + static_cast<size_t>(t) * d + n0;
   const float v0 = P::to_f32(e[0]), v1 = P::to_f32(e[1]), v2 = P::to_f32(e[2]), v3 = P::to_f32(e[3]);
   *reinterpret_cast<float4*>(x + static_cast<size_t>(b) * d + n0) = make_float4(v0, v1, v2, v3);
-  store_act4<P>(act, rec, b, n0, v0, v1, v2, v3);
+  store_resid4<P>(act, rec, b, n0, d, make_float4(v0, v1, v2, v3));
 }
 
 // Tiled projection: out[b][n] = sum_k W[n][k] x[b][k] for rows b < M, fused
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(64) void k_gather_rows(GatherArgs a) {
   const int n0 = 4 * (blockIdx.x * 64 + threadIdx.x);
   if (n0 >= a.d || k >= a.n) return;
   const float4 v = *reinterpret_cast<const float4*>(a.x + static_cast<size_t>(a.src[k]) * a.d + n0);
-  store_act4<P>(static_cast<typename P::elem*>(a.act), a.rec, k, n0, v.x, v.y, v.z, v.w);
+  store_resid4<P>(static_cast<typename P::elem*>(a.act), a.rec, k, n0, a.d, v);
 }
 
 }  // namespace sprk

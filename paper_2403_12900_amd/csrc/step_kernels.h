@@ -48,7 +48,7 @@ __global__ __launch_bounds__(64) void k_embed(EmbedArgs a) {
   const typename P::elem* e = static_cast<const typename P::elem*>(a.emb) + static_cast<size_t>(t) * a.d + n0;
   const float v0 = P::to_f32(e[0]), v1 = P::to_f32(e[1]), v2 = P::to_f32(e[2]), v3 = P::to_f32(e[3]);
   *reinterpret_cast<float4*>(a.x + static_cast<size_t>(b) * a.d + n0) = make_float4(v0, v1, v2, v3);
-  store_act4<P>(static_cast<typename P::elem*>(a.act), a.rec, b, n0, v0, v1, v2, v3);
+  store_resid4<P>(static_cast<typename P::elem*>(a.act), a.rec, b, n0, a.d, make_float4(v0, v1, v2, v3));
 }
 
 struct ArgmaxArgs {

@@ -36,3 +36,18 @@ def test_rows_at_the_edges(n, rows, bf16, kv_bf16):
     say(st)
     assert st["rows"] == 3 * n
     run.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,rows", [(3, 40), (17, 65), (20, 150)])
+def test_model_width_inside_a_k_block(n, rows):
+    """d_model = 208 ends 16 elements into a 32-element K-block: the other 16 of the residual's record must not keep
+    what another projection's record left there, or the fused norms count it."""
+    m = ModelConfig(n_layers=2, d_model=208, n_heads=5, n_kv_heads=5, head_dim=64, d_ff=200, vocab=333)
+    say(f"width inside a K-block: {n} requests, {rows} prompt rows")
+    rng = np.random.default_rng(rows)
+    prompts = [rng.integers(0, m.vocab, size=rows // n + (i < rows % n)).astype(np.int32) for i in range(n)]
+    run = DeviceRun(m, 92, prompts, [3] * n)
+    st = check_against_oracle(run, R.Weights(oracle_shape(m), 92), prompts, [3] * n, range(n), *BF16_TOL)
+    say(st)
+    run.close()
