@@ -101,17 +101,19 @@ __global__ __launch_bounds__(256, 2) void k_tile_gemm(const uint4* W, const uint
   // has its own L2.  XCD x takes the contiguous range of tiles from x * total
   // / 8 in an order that runs over groups of four row tiles, the row tile
   // fastest: the work-groups an XCD holds at a time then work on the same
-  // K-blocks of neighbouring tiles and share both operands in its L2.
+  // K-blocks of neighbouring tiles and share both operands in its L2.  Without
+  // groups every row tile reads the weights again: 15 row tiles of the 70B
+  // shape (1833 rows, four layers) 24.0 ms, 21.3 in groups.
   int nt0, m0, tile;
   {
     const int total = gridDim.x * gridDim.y, b = blockIdx.y * gridDim.x + blockIdx.x;
     const int q = total / 8, r = total % 8, x = b % 8, j = b / 8;
     tile = x * q + min(x, r) + j;
-    const int gm = gridDim.y % 4 == 0 ? 4 : 1;
-    const int per_group = gm * gridDim.x;
+    const int per_group = 4 * gridDim.x;
     const int mg = tile / per_group, rem = tile % per_group;
+    const int gm = min(4, static_cast<int>(gridDim.y) - 4 * mg);  // the last group may be smaller
     nt0 = (rem / gm) * TN;
-    m0 = (mg * gm + rem % gm) * TM * 16;
+    m0 = (4 * mg + rem % gm) * TM * 16;
   }
   const int S = kSplit ? gridDim.z : 1, slice = kSplit ? blockIdx.z : 0;
   const int kb0 = KB * slice / S, kb1 = KB * (slice + 1) / S;

@@ -581,6 +581,13 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   const ActRec rec = act_rec(Rp);
   const SplitRoom room = split_room(workspace_scratch(m));
   spr_status st;
+  auto row_rscale = [&]() {
+    if (d.d > 1024) {
+      k_row_rscale<4><<<C, 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
+    } else {
+      k_row_rscale<1><<<ceil_div(C, 4), 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
+    }
+  };
   const dim3 grid_d(ceil_div(d.d / 4, 64), C);
   k_embed_rows<QKVIn<P>><<<grid_d, 64, 0, m->st>>>(reinterpret_cast<const E*>(p.emb()), p.prow(), p.x(),
                                                    reinterpret_cast<E*>(p.act(0)), d.d, d.V, rec);
@@ -598,7 +605,7 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
         continue;
       }
     }
-    k_row_rscale<<<C, 256, 0, m->st>>>(p.x(), p.rs(), d.d, d.eps);
+    row_rscale();
     {
       EpiQKVRows<P, KP> e{};
       e.M = C;
@@ -635,7 +642,7 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
       EpiResidRows<P> e{C, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       tile_gemm<P>(m->st, p.wo(l), p.act(1), d.nt_o, d.kb_o, Rp, e, room);
     }
-    k_row_rscale<<<C, 256, 0, m->st>>>(p.x(), p.rs(), d.d, d.eps);
+    row_rscale();
     {
       EpiSwiGLURows<P> e{C, rec, p.rs(), reinterpret_cast<E*>(p.act(1))};
       tile_gemm<P>(m->st, p.w13(l), p.act(0), d.nt_13, d.kb_d, Rp, e, room);

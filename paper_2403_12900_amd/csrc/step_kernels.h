@@ -105,22 +105,27 @@ __global__ __launch_bounds__(256) void k_argmax_final(ArgmaxArgs a) {
 }
 
 // RMSNorm scale of each row (unit gains): rs[b] = 1 / sqrt(mean(x_b^2) + eps).
-// One work-group per row: a few hundred rows are bound by the latency of a
-// row's loads, which four waves issue at once (128 rows of 4096: 5.9 us with a
-// wave per row).
-__global__ __launch_bounds__(256) void k_row_rscale(const float* __restrict__ x, float* rs, int d, float eps) {
-  const int b = blockIdx.x;
+// WPR waves per row, 4 / WPR rows per work-group: rows of more than 1024
+// features take all four waves, which issue a row's loads at once (128 rows of
+// 4096: 5.9 us with one wave per row).
+template <int WPR>
+__global__ __launch_bounds__(256) void k_row_rscale(const float* __restrict__ x, float* rs, int M, int d, float eps) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int b = min(static_cast<int>(blockIdx.x) * (4 / WPR) + wave / WPR, M - 1);
   const float* xr = x + static_cast<size_t>(b) * d;
   float s = 0.f;
-  for (int k = 4 * threadIdx.x; k < d; k += 1024) {
+  for (int k = 4 * (lane + 64 * (wave % WPR)); k < d; k += 256 * WPR) {
     const float4 v = *reinterpret_cast<const float4*>(xr + k);
     s = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, s))));
   }
   for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-  __shared__ float part[4];
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) rs[b] = rsqrtf((part[0] + part[1] + part[2] + part[3]) / static_cast<float>(d) + eps);
+  if constexpr (WPR == 4) {
+    __shared__ float part[4];
+    if (lane == 0) part[wave] = s;
+    __syncthreads();
+    s = part[0] + part[1] + part[2] + part[3];
+  }
+  if (lane == 0 && wave % WPR == 0) rs[b] = rsqrtf(s / static_cast<float>(d) + eps);
 }
 
 // out[0 .. n) = 0.

@@ -51,3 +51,19 @@ def test_model_width_inside_a_k_block(n, rows):
     st = check_against_oracle(run, R.Weights(oracle_shape(m), 92), prompts, [3] * n, range(n), *BF16_TOL)
     say(st)
     run.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,d_ff,bf16", [(700, 200, True), (1100, 4096, False), (330, 200, False)])
+def test_prefill_row_tiles_beyond_a_group(rows, d_ff, bf16):
+    """Row tiles that are no multiple of the four of a group (6 of 128 rows, 9 of 128 rows, 6 of 64 rows); 4096
+    feed-forward features over 1100 rows are fp32's large tile, the others its small one."""
+    m = ModelConfig(n_layers=2, d_model=224, n_heads=5, n_kv_heads=5, head_dim=64, d_ff=d_ff, vocab=333, bf16=bf16)
+    say(f"row tiles beyond a group: {rows} prompt rows, d_ff={d_ff} bf16={bf16}")
+    rng = np.random.default_rng(rows)
+    prompts = [rng.integers(0, m.vocab, size=s).astype(np.int32) for s in (rows // 3, rows // 3, rows - 2 * (rows // 3))]
+    run = DeviceRun(m, 93, prompts, [3] * 3)
+    st = check_against_oracle(run, R.Weights(oracle_shape(m), 93), prompts, [3] * 3, range(3),
+                              *(BF16_TOL if bf16 else FP32_TOL))
+    say(st)
+    run.close()
