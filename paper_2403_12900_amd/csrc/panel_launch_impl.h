@@ -57,7 +57,9 @@ struct PanelShapes<true, JT> {
 // 1 to 10 slices): the busiest CU's chain of K-blocks -- its weight tiles, and
 // the activation tiles they share, which every wave reads from LDS -- combined
 // with the HBM time of the matrix, plus the publication of the slices.  Its
-// choices are on average 1.7% slower than the fastest.  Slices of
+// choices are on average 2% slower than the fastest.  More than one work-group
+// per CU is priced up by 5% each (512 tiles x 256 K-blocks, 14 rows: 768
+// work-groups 30 us, 192 take 23.5).  Slices of
 // 64 K-blocks of 256-K-block tiles are priced up: every work-group then
 // starts at a multiple of 64 KiB (512 tiles x 256 K-blocks, 14 rows: four
 // slices 31 us, three 23.5 us).
@@ -74,12 +76,14 @@ inline PanelPick panel_pick(const PanelShape* sh, int n_shapes, int NT, int KB, 
     const size_t quads = sh[i].rt * JT + (norm ? (JT + 3) / 4 : 0);
     for (int S = 1; S <= kMaxSlices && S <= chunks; ++S) {
       if (S > 1 && static_cast<size_t>(groups) * sh[i].nw * S * quads * 256 * sizeof(float) > room) break;
-      const double chain = 1.0 * panel_div(groups * S, kCUs) * panel_div(KB, S) *
+      const int rounds = panel_div(groups * S, kCUs);
+      const double chain = 1.0 * rounds * panel_div(KB, S) *
                            (0.012 * T + (0.0097 + 0.003 * sh[i].nw) * JT * parts);
       const double hbm = 1.62e-4 * NT * KB;
       double us = std::sqrt(chain * chain + hbm * hbm);
       if (S > 1) us += 2.2 + 0.23 * S * sh[i].rt * JT;
       if (S > 1 && KB % 256 == 0 && KB % (64 * S) == 0) us *= 1.25;
+      us *= 1.0 + 0.05 * (rounds - 1);
       if (best.shape < 0 || us < best_us) {
         best = PanelPick{i, S};
         best_us = us;
