@@ -67,9 +67,9 @@ struct KVBlock {
     const uint4* kt = reinterpret_cast<const uint4*>(kc + tile * 16 * HD) + lane;
     const uint4* vt = reinterpret_cast<const uint4*>(vc + tile * 16 * HD) + lane;
 #pragma unroll
-    for (int f = 0; f < NF; ++f) kf[f] = load_weight<true>(kt + f * 64);
+    for (int f = 0; f < NF; ++f) kf[f] = load_weight(kt + f * 64);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) vf[v] = load_weight<true>(vt + v * 64);
+    for (int v = 0; v < NV; ++v) vf[v] = load_weight(vt + v * 64);
   }
 
   // Positions past the context hold stale or never-written cache memory; they

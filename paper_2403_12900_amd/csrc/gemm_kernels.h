@@ -45,16 +45,11 @@ struct StreamDepth {
   static constexpr int value = XW <= 3 ? 8 : XW <= 6 ? 4 : 2;
 };
 
-// Weight fragment load; streaming (nontemporal) loads keep the once-read
-// weights from displacing activations in the caches.
-template <bool kStream>
+// Weight fragment load, nontemporal: the once-read weights do not displace
+// activations in the caches.
 __device__ __forceinline__ uint4 load_weight(const uint4* p) {
-  if constexpr (kStream) {
-    const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-  } else {
-    return *p;
-  }
+  const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
+  return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 // Activation fragments per K-block and 16-row tile: one per part, or, with
@@ -120,10 +115,10 @@ using StreamStageOf = StreamStage<JT, RT, (U / 2 > 0 ? U / 2 : 1), StreamFrags<P
 // pipeline stages.  PK: packed rows (n_rows <= 8, JT = 1, two or three parts).
 // LP: parts per K-block of the activation record (at least P::parts; the
 // first P::parts are used).
-template <class P, int JT, int WAVES, class Epi, int RT, int U, bool kStream, bool PK, int LP = P::parts>
+template <class P, int JT, int WAVES, class Epi, int RT, int U, bool PK, int LP = P::parts>
 __device__ __forceinline__ void stream_gemm_tiles(const uint4* __restrict__ W, const uint4* __restrict__ X, int KB,
-                                                  int Rp, int n_rows, const Epi& epi, int nt0, int wave, int lane,
-                                                  float* red, StreamStageOf<P, JT, RT, U, PK>& s0,
+                                                  int n_rows, const Epi& epi, int nt0, int wave, int lane, float* red,
+                                                  StreamStageOf<P, JT, RT, U, PK>& s0,
                                                   StreamStageOf<P, JT, RT, U, PK>& s1) {
   constexpr int PARTS = P::parts;
   static_assert(!PK || (JT == 1 && PARTS >= 2), "packed rows: one tile of at most 8 rows, two or three parts");
@@ -155,8 +150,8 @@ __device__ __forceinline__ void stream_gemm_tiles(const uint4* __restrict__ W, c
   // K-block's part 0, or past the last K-block's record, inside the buffer)
   // are zeroed after the load.
   constexpr ActRec xr = act_rec(16 * JT);
-  const int xpart = Rp * 4;                  // uint4 per (K-block, part)
-  const int xstep = PK ? 2 * xpart : xpart;  // uint4 between a lane's fragments
+  constexpr int xpart = 64 * JT;                 // uint4 per (K-block, part)
+  constexpr int xstep = PK ? 2 * xpart : xpart;  // uint4 between a lane's fragments
   int xoff[JT];
 #pragma unroll
   for (int j = 0; j < JT; ++j) {
@@ -169,7 +164,7 @@ __device__ __forceinline__ void stream_gemm_tiles(const uint4* __restrict__ W, c
     }
   }
   const bool zero_hi = PK && PARTS == 3 && (lane & 15) >= 8;  // packed (lo | 0): columns 8-15 are zero
-  const size_t xblk = static_cast<size_t>(LP) * xpart;        // uint4 per K-block
+  constexpr size_t xblk = static_cast<size_t>(LP) * xpart;    // uint4 per K-block
   // Operands the epilogue reads from memory (residual, rotary table, block
   // table) are fetched now, by the wave that runs the epilogue, so their
   // latency hides under the weight stream instead of ending the kernel.
@@ -181,7 +176,7 @@ __device__ __forceinline__ void stream_gemm_tiles(const uint4* __restrict__ W, c
 
   auto load1 = [&](Stage& st, int u, int kb) {
 #pragma unroll
-    for (int t = 0; t < RT; ++t) st.a[u][t] = load_weight<kStream>(wp + t * wtile + static_cast<size_t>(kb) * 64);
+    for (int t = 0; t < RT; ++t) st.a[u][t] = load_weight(wp + t * wtile + static_cast<size_t>(kb) * 64);
 #pragma unroll
     for (int j = 0; j < JT; ++j)
 #pragma unroll
@@ -306,15 +301,14 @@ __device__ __forceinline__ void stream_gemm_tiles(const uint4* __restrict__ W, c
   for (int t = 0; t < RT; ++t) epi.template apply<JT>(nt0 + t, acc[t], ssq, lane, pre[t]);
 }
 
-template <class P, int JT, int WAVES, class Epi, int RT = 1, int U = StreamDepth<RT * JT * P::parts>::value,
-          bool kStream = false, bool PK = false>
+template <class P, int JT, int WAVES, class Epi, int RT, int U, bool PK>
 __global__ __launch_bounds__(WAVES * 64) void k_stream_gemm(const uint4* __restrict__ W, const uint4* __restrict__ X,
-                                                            int KB, int Rp, int n_rows, Epi epi) {
+                                                            int KB, int n_rows, Epi epi) {
   __shared__ float red[StreamRed<JT, WAVES, RT>::floats];
   StreamStageOf<P, JT, RT, U, PK> s0, s1;
-  stream_gemm_tiles<P, JT, WAVES, Epi, RT, U, kStream, PK>(W, X, KB, Rp, n_rows, epi, blockIdx.x * RT,
-                                                           __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
-                                                           threadIdx.x & 63, red, s0, s1);
+  stream_gemm_tiles<P, JT, WAVES, Epi, RT, U, PK>(W, X, KB, n_rows, epi, blockIdx.x * RT,
+                                                  __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63,
+                                                  red, s0, s1);
 }
 
 // QKV projection of bf16 models over a three-part record: query tiles (the
@@ -324,19 +318,17 @@ __global__ __launch_bounds__(WAVES * 64) void k_stream_gemm(const uint4* __restr
 // work-group.
 template <int JT, int WAVES, class Epi, int RT, int U2, int U3, bool PK>
 __global__ __launch_bounds__(WAVES * 64) void k_stream_gemm_qkv(const uint4* __restrict__ W,
-                                                                const uint4* __restrict__ X, int KB, int Rp,
-                                                                int n_rows, Epi epi, int q_tiles) {
+                                                                const uint4* __restrict__ X, int KB, int n_rows,
+                                                                Epi epi, int q_tiles) {
   __shared__ float red[StreamRed<JT, WAVES, RT>::floats];
   const int nt0 = blockIdx.x * RT;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (nt0 < q_tiles) {
     StreamStageOf<BF16, JT, RT, U2, PK> s0, s1;
-    stream_gemm_tiles<BF16, JT, WAVES, Epi, RT, U2, true, PK, 3>(W, X, KB, Rp, n_rows, epi, nt0, wave, lane, red, s0,
-                                                                 s1);
+    stream_gemm_tiles<BF16, JT, WAVES, Epi, RT, U2, PK, 3>(W, X, KB, n_rows, epi, nt0, wave, lane, red, s0, s1);
   } else {
     StreamStageOf<BF16x3, JT, RT, U3, PK> s0, s1;
-    stream_gemm_tiles<BF16x3, JT, WAVES, Epi, RT, U3, true, PK, 3>(W, X, KB, Rp, n_rows, epi, nt0, wave, lane, red, s0,
-                                                                   s1);
+    stream_gemm_tiles<BF16x3, JT, WAVES, Epi, RT, U3, PK, 3>(W, X, KB, n_rows, epi, nt0, wave, lane, red, s0, s1);
   }
 }
 

@@ -1,11 +1,12 @@
-// Host-only C entry points over the slot table and workspace layout, built
-// with g++ into a separate test library so the bookkeeping that every
-// spr_prefill / spr_decode_step call runs before enqueueing work can be
+// Host-only C entry points over the slot table, the workspace layout and the
+// launch rules, built with g++ into a separate test library so what every
+// spr_prefill / spr_decode_step call decides before enqueueing work can be
 // exercised without a GPU.  Not part of the device library.
 #include <string>
 #include <vector>
 
 #include "host_state.h"
+#include "launch_rule.h"
 
 namespace {
 thread_local std::string g_err;
@@ -25,6 +26,19 @@ size_t sprh_workspace_bytes(const spr_config* cfg) {
     return 0;
   }
   return spr::layout(d).total;
+}
+
+// gemm_pick: out = {waves, tiles per wave, K-blocks per chunk, slices} of the
+// panel kernel, or zeros for the streaming kernel.
+void sprh_gemm_pick(int f32, int n, int NT, int KB, int parts, int norm, int32_t* out) {
+  const sprk::PanelPick p = sprk::gemm_pick(f32 != 0, n, NT, KB, parts, norm != 0);
+  out[0] = out[1] = out[2] = out[3] = 0;
+  if (p.shape < 0) return;
+  const sprk::PanelShape& s = sprk::panel_shapes(f32 != 0, sprk::row_tiles(n)).s[p.shape];
+  out[0] = s.nw;
+  out[1] = s.rt;
+  out[2] = s.uc;
+  out[3] = p.slices;
 }
 
 void* sprh_new(const spr_config* cfg) {

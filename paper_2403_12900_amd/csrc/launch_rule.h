@@ -1,0 +1,168 @@
+// The rules that pick a projection's kernel, tile shape and K slices from its
+// sizes.  Pure C++ (no HIP): the launches and the host test library share them.
+//
+// Sizes: NT 16-row weight tiles, KB K-blocks per tile, JT 16-row activation
+// tiles, parts = activation parts (fp32 1, bf16 2, bf16 QKV input 3).
+#pragma once
+
+#include <cmath>
+#include <cstddef>
+#include <cstdint>
+#include <iterator>
+
+#include "host_state.h"
+
+namespace sprk {
+
+inline int rule_div(int a, int b) { return (a + b - 1) / b; }
+
+// 16-row activation tiles of a pass over n rows (kernels exist for these
+// counts).
+inline int row_tiles(int n) {
+  const int t = (n + 15) / 16;
+  return t <= 4 ? t : t <= 6 ? 6 : 8;
+}
+
+// Shapes of k_panel_gemm by row tiles: waves, tiles per wave, K-blocks per
+// chunk.  A work-group's NW x RT tiles are what one activation byte moved into
+// LDS serves; the set covers group sizes that divide the usual tile counts
+// into close to 256 work-groups (one per CU) with few slices.
+struct PanelShape {
+  int nw, rt, uc;
+};
+template <bool kF32, int JT>
+struct PanelShapes {
+  static constexpr PanelShape s[] = {{4, 1, 1}, {8, 1, 1}, {8, 2, 1}, {4, 3, 1}};  // 65 to 128 rows
+};
+template <>
+struct PanelShapes<false, 1> {
+  static constexpr PanelShape s[] = {{4, 1, 4}, {6, 1, 2}, {4, 2, 2}, {7, 2, 2}};
+};
+template <>
+struct PanelShapes<false, 2> {
+  static constexpr PanelShape s[] = {{4, 1, 2}, {6, 1, 2}, {8, 1, 2}, {7, 2, 2}};
+};
+template <>
+struct PanelShapes<false, 3> {
+  static constexpr PanelShape s[] = {{4, 1, 2}, {8, 1, 2}, {4, 2, 2}, {6, 2, 2}, {7, 2, 2}};
+};
+template <>
+struct PanelShapes<false, 4> {
+  static constexpr PanelShape s[] = {{4, 1, 2}, {8, 1, 2}, {4, 2, 2}, {6, 2, 2}, {7, 2, 2}};
+};
+// fp32 models (no full-size fp32 model is served): one shape.
+template <int JT>
+struct PanelShapes<true, JT> {
+  static constexpr PanelShape s[] = {{4, 1, 1}};
+};
+
+struct PanelShapeSet {
+  const PanelShape* s;
+  int n;
+};
+inline PanelShapeSet panel_shapes(bool f32, int JT) {
+  auto set = [](const auto& a) { return PanelShapeSet{a, static_cast<int>(std::size(a))}; };
+  if (f32) return set(PanelShapes<true, 1>::s);
+  switch (JT) {
+    case 1: return set(PanelShapes<false, 1>::s);
+    case 2: return set(PanelShapes<false, 2>::s);
+    case 3: return set(PanelShapes<false, 3>::s);
+    case 4: return set(PanelShapes<false, 4>::s);
+    default: return set(PanelShapes<false, 8>::s);
+  }
+}
+
+// Shape (index) and slices of a panel launch: the least of an estimated time
+// in microseconds, fitted to 2600 timings of the kernel on MI355X (the
+// projections of the 7B, 13B and 70B shapes and uneven ones, 14 to 128 rows,
+// 1 to 10 slices): the busiest CU's chain of K-blocks -- its weight tiles, and
+// the activation tiles they share, which every wave reads from LDS -- combined
+// with the HBM time of the matrix, plus the publication of the slices.  Its
+// choices are on average 2% slower than the fastest.  More than one work-group
+// per CU is priced up by 5% each (512 tiles x 256 K-blocks, 14 rows: 768
+// work-groups 30 us, 192 take 23.5).  Slices of
+// 64 K-blocks of 256-K-block tiles are priced up: every work-group then
+// starts at a multiple of 64 KiB (512 tiles x 256 K-blocks, 14 rows: four
+// slices 31 us, three 23.5 us).
+struct PanelPick {
+  int shape = -1, slices = 1;
+  double us = 0;  // the estimate
+};
+inline PanelPick panel_pick(bool f32, int NT, int KB, int JT, int parts, bool norm) {
+  constexpr int kCUs = 256, kMaxSlices = 16;
+  const PanelShapeSet sh = panel_shapes(f32, JT);
+  const size_t room = JT <= 4 ? spr::kSplitPartBytes : spr::kSplitPartBytesWide;
+  PanelPick best;
+  for (int i = 0; i < sh.n; ++i) {
+    const PanelShape& s = sh.s[i];
+    const int T = s.nw * s.rt, groups = rule_div(NT, T), chunks = rule_div(KB, s.uc);
+    const size_t quads = s.rt * JT + (norm ? (JT + 3) / 4 : 0);
+    for (int S = 1; S <= kMaxSlices && S <= chunks; ++S) {
+      if (S > 1 && static_cast<size_t>(groups) * s.nw * S * quads * 256 * sizeof(float) > room) break;
+      const int rounds = rule_div(groups * S, kCUs);
+      const double chain = 1.0 * rounds * rule_div(KB, S) * (0.012 * T + (0.0097 + 0.003 * s.nw) * JT * parts);
+      const double hbm = 1.62e-4 * NT * KB;
+      double us = std::sqrt(chain * chain + hbm * hbm);
+      if (S > 1) us += 2.2 + 0.23 * S * s.rt * JT;
+      if (S > 1 && KB % 256 == 0 && KB % (64 * S) == 0) us *= 1.25;
+      us *= 1.0 + 0.05 * (rounds - 1);
+      if (best.shape < 0 || us < best.us) best = PanelPick{i, S, us};
+    }
+  }
+  return best;
+}
+
+// Rows up to which a bf16 pass takes the register-streaming kernel, packed.
+constexpr int kPackedRows = 8;
+
+// Whether the streaming kernel takes its wide form: one-wave work-groups of
+// two tiles.
+inline bool stream_wide(int NT, int JT, int parts) {
+  return JT == 1 && parts < 3 && NT >= 1024 && NT % 2 == 0;
+}
+
+// Estimated time (us) of the streaming kernel's four-wave form at one to four
+// row tiles, and of the panel kernel on the same scale, fitted to 600 timings
+// on MI355X: all five projections of models of 256 to 5120 features, fp32 and
+// bf16, 9 to 64 rows.  Streaming, a work-group per tile reads the whole
+// activation, so its time grows with NT x KB x JT; the panel kernel starts
+// with about three microseconds of staging and barriers, and an fp32 fragment
+// costs it four MFMAs, which the pick's estimate prices as one.
+inline double stream_us(bool f32, int NT, int KB, int JT, int parts) {
+  const double rounds = rule_div(NT, 256), act = JT * parts, fill = NT / 256.0;
+  if (f32)
+    return 2.1 + 0.44 * JT +
+           KB * (0.0028 + 0.011 * rounds + act * (0.021 * rounds + 0.0057 * fill + (fill > 1 ? 0.0313 * (fill - 1) : 0)));
+  return 2.0 + 0.38 * JT + KB * (0.026 * rounds + act * (0.002 + 0.0061 * rounds + 0.0052 * fill));
+}
+inline double panel_us(bool f32, const PanelPick& p) { return f32 ? 2.6 + 1.55 * p.us : 3.2 + 0.7 * p.us; }
+
+// The kernel of a projection of n rows: streaming (panel.shape < 0) or panel.
+//   * up to 8 rows: streaming.  A bf16 matrix of kPanelMatrix K-block tiles
+//     (576 MB) or more, whose tiles split evenly over the CUs whatever the
+//     group size, takes the panel kernel at any row count (70B gate/up, 3
+//     rows: 135 us against 143; the 7B shape's matrices are 0 to 2 us faster
+//     streamed);
+//   * one row tile of fp32: streaming (the panel kernel took 1.2 to 2.9 times
+//     as long, but for 300 tiles x 260 K-blocks, 26.3 us against 27.6);
+//   * one row tile of bf16 in the wide form: streaming below 96 K-blocks (9
+//     rows, 2000 tiles x 64: 21.1 us, panel 26.0; 1024 x 96: 18.4, panel 17.8);
+//   * up to 64 rows otherwise: the lesser estimate.  It is wrong by 0.5%
+//     (bf16) and 0.2% (fp32) of the time on average; always taking the panel
+//     kernel would cost 12% and 35% (fp32 down, 64 tiles x 64, 24 rows: 6.2 us
+//     streamed, panel 8.7; bf16 down, 256 x 344, 24 rows: 27.0, panel 21.6);
+//   * more rows: panel.
+constexpr int64_t kPanelMatrix = 576 << 10;
+inline PanelPick gemm_pick(bool f32, int n, int NT, int KB, int parts, bool norm) {
+  const int JT = row_tiles(n);
+  const PanelPick stream;
+  if (n <= kPackedRows) {
+    return !f32 && int64_t{NT} * KB >= kPanelMatrix ? panel_pick(f32, NT, KB, JT, parts, norm) : stream;
+  }
+  if (JT == 1 && (f32 || (stream_wide(NT, JT, parts) && KB < 96))) return stream;
+  const PanelPick p = panel_pick(f32, NT, KB, JT, parts, norm);
+  if (JT > 4 || stream_wide(NT, JT, parts)) return p;
+  return panel_us(f32, p) < stream_us(f32, NT, KB, JT, parts) ? p : stream;
+}
+
+}  // namespace sprk

@@ -1,10 +1,10 @@
-// Launch of the panel kernel (panel_kernels.h) for a projection of more than
-// eight rows.  The kernel's instantiations are compiled in translation units
-// of their own (panel_*.hip).
+// Launch of the panel kernel (panel_kernels.h).  The kernel's instantiations
+// are compiled in translation units of their own (panel_*.hip).
 #pragma once
 
 #include <type_traits>
 
+#include "launch_rule.h"
 #include "panel_kernels.h"
 
 namespace sprk {
@@ -25,17 +25,11 @@ struct SplitRoom {
   int n_cnt = 0;
 };
 
-// 16-row activation tiles of a pass over n rows (panel kernels exist for these
-// counts).
-inline int row_tiles(int n) {
-  const int t = (n + 15) / 16;
-  return t <= 4 ? t : t <= 6 ? 6 : 8;
-}
-
 // Enqueues the projection of epi.n_rows rows (at most kRows; the activation
-// record has row_tiles(n_rows) row tiles).  P: activation format of the input.
+// record has row_tiles(n_rows) row tiles) in the shape that gemm_pick chose.
+// P: activation format of the input.
 template <class P, class Epi>
 void launch_panel_gemm(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, const Epi& epi,
-                       const SplitRoom& room);
+                       const SplitRoom& room, const PanelPick& pick);
 
 }  // namespace sprk

@@ -7,8 +7,8 @@ using EpiQKVbf = EpiQKV<BF16, F32>;
 using EpiQKVff = EpiQKV<F32, F32>;
 
 template void sprk::launch_panel_gemm<BF16x3, EpiQKVbb>(hipStream_t, int, const uint4*, const uint4*, int,
-                                            const EpiQKVbb&, const SplitRoom&);
+                                            const EpiQKVbb&, const SplitRoom&, const PanelPick&);
 template void sprk::launch_panel_gemm<BF16x3, EpiQKVbf>(hipStream_t, int, const uint4*, const uint4*, int,
-                                            const EpiQKVbf&, const SplitRoom&);
+                                            const EpiQKVbf&, const SplitRoom&, const PanelPick&);
 template void sprk::launch_panel_gemm<F32, EpiQKVff>(hipStream_t, int, const uint4*, const uint4*, int,
-                                            const EpiQKVff&, const SplitRoom&);
+                                            const EpiQKVff&, const SplitRoom&, const PanelPick&);

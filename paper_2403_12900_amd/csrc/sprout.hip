@@ -219,9 +219,6 @@ DecodeScratch workspace_scratch(const spr_model* m) {
   return DecodeScratch{p.part(), p.cnt(), p.amax(), spr::kMaxSplits, m->lay.part_floats, m->lay.n_cnt};
 }
 
-// Rows up to which a decode pass takes the register-streaming kernel.
-constexpr int kStreamRows = 8;
-
 SplitRoom split_room(const DecodeScratch& sc) { return SplitRoom{sc.part, sc.cnt, sc.part_floats, sc.n_cnt}; }
 
 template <class P>
@@ -260,19 +257,34 @@ struct RowSet {
   int hist_idx[kRows];  // token-history index of the row's token, -1 = none
 };
 
-// Projection of a pass over epi.n_rows rows (activation record of row_tiles
-// row tiles): up to kStreamRows rows on the register-streaming kernel, more on
-// the panel kernel.  A matrix of kPanelMatrix K-block tiles (576 MB) or more,
-// whose tiles split evenly over the CUs whatever the group size, takes the
-// panel kernel at any row count (70B gate/up, 3 rows: 135 us against 143; the
-// 7B shape's matrices are 0 to 2 us faster streamed).  Streaming shapes, from
-// sweeps over the 7B projections on MI355X at 1 to 8 rows:
-//   * wide projections (>= 1024 16-row tiles: gate/up, LM head): one-wave
-//     work-groups, each streaming two whole tiles over the full K -- long
-//     contiguous streams and no cross-wave reduction;
+// Register-streaming projection of epi.n_rows rows (activation record of JT
+// row tiles).  Shapes from sweeps over the 7B projections on MI355X:
+//   * wide projections (>= 1024 16-row tiles: gate/up, LM head) of one row
+//     tile: one-wave work-groups, each streaming two whole tiles over the full
+//     K -- long contiguous streams and no cross-wave reduction;
 //   * everything else: four waves split K for one tile.
-// bf16 activations are packed (two parts per fragment, at most 8 rows).
-constexpr int64_t kPanelMatrix = 576 << 10;
+// PK: packed rows (bf16, at most 8 rows, two activation parts per fragment).
+template <class P, int JT, bool PK, class Epi>
+void launch_stream(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, const Epi& epi) {
+  const int n = epi.n_rows;
+  constexpr int XF = StreamFrags<P, PK>::value;  // activation fragments per K-block and row tile
+  if constexpr (P::parts == 3) {                 // QKV: query tiles take two of the three parts
+    constexpr int X2 = StreamFrags<BF16, PK>::value;
+    k_stream_gemm_qkv<JT, 4, Epi, 1, StreamDepth<JT * X2>::value, StreamDepth<JT * XF>::value, PK>
+        <<<NT, 256, 0, st>>>(w, x, KB, n, epi, epi.H * epi.hd / 16);
+  } else {
+    if constexpr (JT == 1) {
+      if (stream_wide(NT, JT, P::parts)) {
+        k_stream_gemm<P, 1, 1, Epi, 2, 8, PK><<<NT / 2, 64, 0, st>>>(w, x, KB, n, epi);
+        return;
+      }
+    }
+    k_stream_gemm<P, JT, 4, Epi, 1, StreamDepth<JT * XF>::value, PK><<<NT, 256, 0, st>>>(w, x, KB, n, epi);
+  }
+}
+
+// Projection of a pass over epi.n_rows rows, on the kernel that gemm_pick
+// chooses.
 template <class P, class Epi>
 spr_status launch_gemm(spr_model* m, int NT, const char* W, const char* X, int KB, const Epi& epi,
                        const SplitRoom& room) {
@@ -280,22 +292,25 @@ spr_status launch_gemm(spr_model* m, int NT, const char* W, const char* X, int K
   const uint4* x = reinterpret_cast<const uint4*>(X);
   const hipStream_t st = m->st;
   const int n = epi.n_rows;
-  if (n > kStreamRows || (P::parts >= 2 && int64_t{NT} * KB >= kPanelMatrix)) {
-    launch_panel_gemm<P, Epi>(st, NT, w, x, KB, epi, room);
+  const PanelPick pick = gemm_pick(std::is_same_v<P, F32>, n, NT, KB, P::parts, Epi::kNorm);
+  if (pick.shape >= 0) {
+    launch_panel_gemm<P, Epi>(st, NT, w, x, KB, epi, room, pick);
     SPR_LAUNCHED(m, "k_panel_gemm");
     return SPR_OK;
   }
-  constexpr int Rp = 16;
-  constexpr bool PK = P::parts >= 2;
-  constexpr int XF = StreamFrags<P, PK>::value;  // activation fragments per K-block
-  if constexpr (P::parts == 3) {                 // QKV: query tiles take two of the three parts
-    constexpr int X2 = StreamFrags<BF16, PK>::value;
-    k_stream_gemm_qkv<1, 4, Epi, 1, StreamDepth<X2>::value, StreamDepth<XF>::value, PK>
-        <<<NT, 256, 0, st>>>(w, x, KB, Rp, n, epi, epi.H * epi.hd / 16);
-  } else if (NT >= 1024 && NT % 2 == 0) {
-    k_stream_gemm<P, 1, 1, Epi, 2, 8, true, PK><<<NT / 2, 64, 0, st>>>(w, x, KB, Rp, n, epi);
-  } else {
-    k_stream_gemm<P, 1, 4, Epi, 1, StreamDepth<XF>::value, true, PK><<<NT, 256, 0, st>>>(w, x, KB, Rp, n, epi);
+  switch (row_tiles(n)) {
+    case 1:
+      if constexpr (P::parts >= 2) {
+        if (n <= kPackedRows) {
+          launch_stream<P, 1, true>(st, NT, w, x, KB, epi);
+          break;
+        }
+      }
+      launch_stream<P, 1, false>(st, NT, w, x, KB, epi);
+      break;
+    case 2: launch_stream<P, 2, false>(st, NT, w, x, KB, epi); break;
+    case 3: launch_stream<P, 3, false>(st, NT, w, x, KB, epi); break;
+    default: launch_stream<P, 4, false>(st, NT, w, x, KB, epi); break;
   }
   SPR_LAUNCHED(m, "k_stream_gemm");
   return SPR_OK;

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void k_read_stream(const uint4* __restrict__ p
     const uint4* q = p + c * kChunk + threadIdx.x;
     uint4 v[kReadUnroll];
 #pragma unroll
-    for (int u = 0; u < kReadUnroll; ++u) v[u] = load_weight<true>(q + u * 256);
+    for (int u = 0; u < kReadUnroll; ++u) v[u] = load_weight(q + u * 256);
 #pragma unroll
     for (int u = 0; u < kReadUnroll; ++u) acc ^= v[u].x ^ v[u].y ^ v[u].z ^ v[u].w;
   }
