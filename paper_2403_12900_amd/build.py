@@ -33,8 +33,8 @@ def _run(cmd, verbose):
 
 
 # Translation units of libsprout.so, the slowest to compile first; compiled in parallel.
-SOURCES = ["panel_qkv.hip", "panel_resid.hip", "panel_mlp.hip", "tile_qkv.hip", "tile_resid.hip", "tile_mlp.hip",
-           "sprout.hip", "host_state.cpp"]
+SOURCES = ["panel_qkv.hip", "panel_qkv_rows.hip", "panel_mlp.hip", "sprout.hip", "panel_resid.hip", "tile_qkv.hip",
+           "tile_resid.hip", "tile_mlp.hip", "host_state.cpp"]
 
 
 def build(verbose: bool = True) -> None:

@@ -359,11 +359,16 @@ __device__ __forceinline__ void store_resid4(typename P::elem* act, const ActRec
 // order (ktile_offset) and the V tile is transposed into the operand order of
 // the P V product (vtile_offset), so the attention kernel reads both with
 // 16-byte loads straight into MFMA operands.
-template <class P, class KP = P>
+// kRowScale: the rows' RMSNorm scales come from rs (k_row_rscale, from the
+// fp32 residual), not from the sums of squares of the activation parts.
+// Prefill chunks take them so, as the tiled prefill kernels do: the parts'
+// Gram products leave out lo.lo, which puts a sum of squares 2.7e-6 low.
+template <class P, class KP = P, bool kRowScale = false>
 struct EpiQKV {
-  static constexpr bool kNorm = true;
+  static constexpr bool kNorm = !kRowScale;
   int n_rows, H, Hkv, hd, mb, dnorm;
   float eps;
+  const float* rs;              // kRowScale: [rows]
   float* q;                     // [rows][H * hd]
   typename KP::elem* kc;        // this layer's K blocks (KV-cache format KP)
   typename KP::elem* vc;        // this layer's V blocks
@@ -372,11 +377,12 @@ struct EpiQKV {
   RowSlotPos rows;
 
   // Per row tile of a lane: the rotary (cos, sin) pairs of its four features
-  // (q and k rows) and the KV block its position falls in (k and v rows).
-  // Lanes of rows past n_rows fetch row 0's.
+  // (q and k rows), the KV block its position falls in (k and v rows) and, if
+  // given, the row's scale.  Lanes of rows past n_rows fetch row 0's.
   struct Pre {
     float4 cs[kRows / 16];
     int blk[kRows / 16];
+    float s[kRowScale ? kRows / 16 : 1];
   };
   template <int JT>
   __device__ __forceinline__ Pre prefetch(int nt, int lane) const {
@@ -388,6 +394,7 @@ struct EpiQKV {
       const int b = 16 * j + (lane & 15);
       const int bb = b < n_rows ? b : 0;
       const int p = rows.pos[bb];
+      if constexpr (kRowScale) pr.s[j] = rs[bb];
       if (n0 < qr + kr) {
         const int dd = (n0 < qr ? n0 : n0 - qr) % hd;
         pr.cs[j] = *reinterpret_cast<const float4*>(rope + static_cast<size_t>(p) * (hd / 2) + dd / 2);
@@ -405,7 +412,7 @@ struct EpiQKV {
     for (int j = 0; j < JT; ++j) {
       const int b = 16 * j + (lane & 15);
       if (b >= n_rows) continue;
-      const float s = rsqrtf(ssq[j] / static_cast<float>(dnorm) + eps);
+      const float s = kRowScale ? pr.s[kRowScale ? j : 0] : rsqrtf(ssq[j] / static_cast<float>(dnorm) + eps);
       float v0 = acc[j][0] * s, v1 = acc[j][1] * s, v2 = acc[j][2] * s, v3 = acc[j][3] * s;
       const int p = rows.pos[b];
       if (n0 < qr + kr) {
@@ -490,29 +497,40 @@ struct EpiResid {
 };
 
 // Gate/up projection (interleaved rows, see wgen_kernels.h): RMSNorm scale,
-// then h = SiLU(gate) * up for two features per lane.
-template <class P>
+// then h = SiLU(gate) * up for two features per lane.  kRowScale: see EpiQKV.
+template <class P, bool kRowScale = false>
 struct EpiSwiGLU {
-  static constexpr bool kNorm = true;
+  static constexpr bool kNorm = !kRowScale;
   int n_rows, dnorm;
   ActRec rec;                   // layout of act
   float eps;
+  const float* rs;              // kRowScale: [rows]
   typename P::elem* act;        // h, K-block-major over d_ff
 
-  struct Pre {};
+  struct Pre {
+    float s[kRowScale ? kRows / 16 : 1];
+  };
   template <int JT>
-  __device__ __forceinline__ Pre prefetch(int, int) const {
-    return {};
+  __device__ __forceinline__ Pre prefetch(int, int lane) const {
+    Pre pr;
+    if constexpr (kRowScale) {
+#pragma unroll
+      for (int j = 0; j < JT; ++j) {
+        const int b = 16 * j + (lane & 15);
+        pr.s[j] = rs[b < n_rows ? b : 0];
+      }
+    }
+    return pr;
   }
 
   template <int JT>
-  __device__ __forceinline__ void apply(int nt, const f32x4_t* acc, const float* ssq, int lane, const Pre&) const {
+  __device__ __forceinline__ void apply(int nt, const f32x4_t* acc, const float* ssq, int lane, const Pre& pr) const {
     const int j0 = 8 * nt + 2 * (lane >> 4);
 #pragma unroll
     for (int j = 0; j < JT; ++j) {
       const int b = 16 * j + (lane & 15);
       if (b >= n_rows) continue;
-      const float s = rsqrtf(ssq[j] / static_cast<float>(dnorm) + eps);
+      const float s = kRowScale ? pr.s[kRowScale ? j : 0] : rsqrtf(ssq[j] / static_cast<float>(dnorm) + eps);
       const float g0 = acc[j][0] * s, g1 = acc[j][1] * s, u0 = acc[j][2] * s, u1 = acc[j][3] * s;
       const float h0 = g0 / (1.f + __expf(-g0)) * u0;
       const float h1 = g1 / (1.f + __expf(-g1)) * u1;

@@ -11,8 +11,8 @@ namespace sprk {
 // Whether an epilogue is QKV's.
 template <class E>
 struct IsQKV : std::false_type {};
-template <class F, class KP>
-struct IsQKV<EpiQKV<F, KP>> : std::true_type {};
+template <class F, class KP, bool RS>
+struct IsQKV<EpiQKV<F, KP, RS>> : std::true_type {};
 
 template <class P, int JT, size_t I, class Epi>
 void launch_panel_shape(hipStream_t st, int NT, const uint4* w, const uint4* x, int KB, const Epi& epi, int S,

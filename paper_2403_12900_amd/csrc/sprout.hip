@@ -21,7 +21,8 @@
 //   k_attn_prefill (causal, 16 queries per MFMA), k_tile_gemm<EpiResidRows>,
 //   k_row_rscale, k_tile_gemm<EpiSwiGLURows>, k_tile_gemm<EpiResidRows>;
 //   then k_gather_rows of the rows that end a prompt, and the decode LM head
-//   (bf16 chunks of at most 128 rows run a decode pass's projections instead).
+//   (bf16 chunks of at most 128 rows run a decode pass's projections instead,
+//   with the row scales of k_row_rscale).
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -367,13 +368,27 @@ int attn_blocks_per_cu(const spr::Dims& d) {
   return o;
 }
 
-// QKV projection of layer l over n rows (a decode pass, or a prefill chunk of
-// as many rows).
-template <class P, class KP>
+// RMSNorm scales of the first C residual rows (prefill).
+void launch_row_rscale(spr_model* m, int C) {
+  const spr::Dims& d = m->d;
+  Ptrs p{m->ws, &m->lay};
+  if (d.d > 1024) {
+    k_row_rscale<4><<<C, 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
+  } else {
+    k_row_rscale<1><<<ceil_div(C, 4), 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
+  }
+}
+
+// QKV projection of layer l over n rows: a decode pass, or (kPrefill) a
+// prefill chunk of as many rows, whose norms take their scales from the fp32
+// residual.
+template <class P, class KP, bool kPrefill>
 spr_status qkv_projection(spr_model* m, int l, int n, const RowSlotPos& rows, const SplitRoom& room) {
   const spr::Dims& d = m->d;
   Ptrs p{m->ws, &m->lay};
-  EpiQKV<P, KP> e{};
+  if constexpr (kPrefill) launch_row_rscale(m, n);
+  EpiQKV<P, KP, kPrefill> e{};
+  e.rs = p.rs();
   e.n_rows = n;
   e.H = d.H;
   e.Hkv = d.Hkv;
@@ -391,8 +406,9 @@ spr_status qkv_projection(spr_model* m, int l, int n, const RowSlotPos& rows, co
 }
 
 // O, gate/up and down projections of layer l over n rows, from the attention
-// output to the next layer's QKV input (qkv_next) or the LM head's.
-template <class P>
+// output to the next layer's QKV input (qkv_next) or the LM head's.  kPrefill:
+// as in qkv_projection.
+template <class P, bool kPrefill>
 spr_status mlp_projections(spr_model* m, int l, int n, bool qkv_next, const SplitRoom& room) {
   const spr::Dims& d = m->d;
   Ptrs p{m->ws, &m->lay};
@@ -403,8 +419,9 @@ spr_status mlp_projections(spr_model* m, int l, int n, bool qkv_next, const Spli
     EpiResid<P> e{n, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
     if ((st = launch_gemm<P>(m, d.nt_o, p.wo(l), p.act(1), d.kb_o, e, room)) != SPR_OK) return st;
   }
+  if constexpr (kPrefill) launch_row_rscale(m, n);
   {
-    EpiSwiGLU<P> e{n, d.d, rec, d.eps, reinterpret_cast<E*>(p.act(1))};
+    EpiSwiGLU<P, kPrefill> e{n, d.d, rec, d.eps, p.rs(), reinterpret_cast<E*>(p.act(1))};
     if ((st = launch_gemm<P>(m, d.nt_13, p.w13(l), p.act(0), d.kb_d, e, room)) != SPR_OK) return st;
   }
   if (qkv_next) {
@@ -485,11 +502,11 @@ spr_status forward(spr_model* m, const RowSet& rs, const int32_t* tok_in, int32_
   const SplitRoom room = split_room(sc);
   spr_status st;
   for (int l = 0; l < d.L; ++l) {
-    if ((st = qkv_projection<P, KP>(m, l, n, sp, room)) != SPR_OK) return st;
+    if ((st = qkv_projection<P, KP, false>(m, l, n, sp, room)) != SPR_OK) return st;
     const AttnArgs a = attention_args<P, KP>(m, l, rs, rec, bpw, order, rounds, p.act(1), sc);
     st = d.hd == 128 ? launch_attention<P, KP, 128>(m, a) : launch_attention<P, KP, 64>(m, a);
     if (st != SPR_OK) return st;
-    if ((st = mlp_projections<P>(m, l, n, l + 1 < d.L, room)) != SPR_OK) return st;
+    if ((st = mlp_projections<P, false>(m, l, n, l + 1 < d.L, room)) != SPR_OK) return st;
   }
   {
     EpiLogits<P> e{};
@@ -532,7 +549,7 @@ spr_status launch_projection(spr_model* m, int projection, int layer, int n) {
       return launch_gemm<P>(m, d.nt_o, p.wo(layer), p.act(1), d.kb_o, e, room);
     }
     case 2: {
-      EpiSwiGLU<P> e{n, d.d, rec, d.eps, reinterpret_cast<E*>(p.act(1))};
+      EpiSwiGLU<P> e{n, d.d, rec, d.eps, nullptr, reinterpret_cast<E*>(p.act(1))};
       return launch_gemm<P>(m, d.nt_13, p.w13(layer), p.act(0), d.kb_d, e, room);
     }
     case 3: {  // as in every layer but the last
@@ -586,23 +603,15 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   Ptrs p{m->ws, &m->lay};
   using E = typename P::elem;
   const int C = ch.C;
-  // A bf16 chunk that a decode pass could hold runs its projections as a
-  // decode pass does: they are still bound by the weight stream, and the panel
-  // kernel needs no row scales beforehand (panel / tiled: 8 layers of the 7B
-  // shape, 96 rows 1.50 / 1.83 ms, 128 rows 1.82 / 1.87 ms; 8 layers of 13B,
-  // 96 rows 1.98 / 2.39 ms, 128 rows 2.58 / 2.43 ms).
+  // A bf16 chunk that a decode pass could hold runs its projections on the
+  // kernels of a decode pass: they are still bound by the weight stream (panel
+  // / tiled: 8 layers of the 7B shape, 96 rows 1.50 / 1.83 ms, 128 rows 1.82 /
+  // 1.87 ms; 8 layers of 13B, 96 rows 1.98 / 2.39 ms, 128 rows 2.58 / 2.43 ms).
   const bool small = P::parts >= 2 && C <= kRows;
   const int Rp = small ? 16 * row_tiles(C) : 128 * ceil_div(C, 128);
   const ActRec rec = act_rec(Rp);
   const SplitRoom room = split_room(workspace_scratch(m));
   spr_status st;
-  auto row_rscale = [&]() {
-    if (d.d > 1024) {
-      k_row_rscale<4><<<C, 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
-    } else {
-      k_row_rscale<1><<<ceil_div(C, 4), 256, 0, m->st>>>(p.x(), p.rs(), C, d.d, d.eps);
-    }
-  };
   const dim3 grid_d(ceil_div(d.d / 4, 64), C);
   k_embed_rows<QKVIn<P>><<<grid_d, 64, 0, m->st>>>(reinterpret_cast<const E*>(p.emb()), p.prow(), p.x(),
                                                    reinterpret_cast<E*>(p.act(0)), d.d, d.V, rec);
@@ -610,17 +619,17 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   for (int l = 0; l < d.L; ++l) {
     if constexpr (P::parts >= 2) {
       if (small) {
-        if ((st = qkv_projection<P, KP>(m, l, C, ch.sp, room)) != SPR_OK) return st;
+        if ((st = qkv_projection<P, KP, true>(m, l, C, ch.sp, room)) != SPR_OK) return st;
         if (d.hd == 128) {
           launch_attn_prefill<P, KP, 128>(m, l, ch, rec);
         } else {
           launch_attn_prefill<P, KP, 64>(m, l, ch, rec);
         }
-        if ((st = mlp_projections<P>(m, l, C, true, room)) != SPR_OK) return st;
+        if ((st = mlp_projections<P, true>(m, l, C, true, room)) != SPR_OK) return st;
         continue;
       }
     }
-    row_rscale();
+    launch_row_rscale(m, C);
     {
       EpiQKVRows<P, KP> e{};
       e.M = C;
@@ -657,7 +666,7 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
       EpiResidRows<P> e{C, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
       tile_gemm<P>(m->st, p.wo(l), p.act(1), d.nt_o, d.kb_o, Rp, e, room);
     }
-    row_rscale();
+    launch_row_rscale(m, C);
     {
       EpiSwiGLURows<P> e{C, rec, p.rs(), reinterpret_cast<E*>(p.act(1))};
       tile_gemm<P>(m->st, p.w13(l), p.act(0), d.nt_13, d.kb_d, Rp, e, room);
