@@ -138,11 +138,13 @@ inline double stream_us(bool f32, int NT, int KB, int JT, int parts) {
 inline double panel_us(bool f32, const PanelPick& p) { return f32 ? 2.6 + 1.55 * p.us : 3.2 + 0.7 * p.us; }
 
 // The kernel of a projection of n rows: streaming (panel.shape < 0) or panel.
-//   * up to 8 rows: streaming.  A bf16 matrix of kPanelMatrix K-block tiles
-//     (576 MB) or more, whose tiles split evenly over the CUs whatever the
-//     group size, takes the panel kernel at any row count (70B gate/up, 3
-//     rows: 135 us against 143; the 7B shape's matrices are 0 to 2 us faster
-//     streamed);
+//   * up to 8 rows: streaming, but for bf16 matrices whose 14-tile work-groups
+//     (7 waves x 2) fill three quarters or more of the CUs in one round, over
+//     192 K-blocks or more.  Panel against streamed, 1 row: 2688 x 256 108 us /
+//     114, 3584 x 256 (70B gate/up) 133 / 140, 3200 x 192 91 / 95.  Outside:
+//     2304 x 256 102 / 97 and 2560 x 256 106 / 104 (CUs left idle), 4608 x 256
+//     209 / 185, 5120 x 192 165 / 146 and 8016 x 256 (an LM head) 340 / 306 (a
+//     second round), 1376 x 128 30.2 / 29.7; 3840 x 160 equal;
 //   * one row tile of fp32: streaming (the panel kernel took 1.2 to 2.9 times
 //     as long, but for 300 tiles x 260 K-blocks, 26.3 us against 27.6);
 //   * one row tile of bf16 in the wide form: streaming below 96 K-blocks (9
@@ -152,12 +154,12 @@ inline double panel_us(bool f32, const PanelPick& p) { return f32 ? 2.6 + 1.55 *
 //     kernel would cost 12% and 35% (fp32 down, 64 tiles x 64, 24 rows: 6.2 us
 //     streamed, panel 8.7; bf16 down, 256 x 344, 24 rows: 27.0, panel 21.6);
 //   * more rows: panel.
-constexpr int64_t kPanelMatrix = 576 << 10;
 inline PanelPick gemm_pick(bool f32, int n, int NT, int KB, int parts, bool norm) {
   const int JT = row_tiles(n);
   const PanelPick stream;
   if (n <= kPackedRows) {
-    return !f32 && int64_t{NT} * KB >= kPanelMatrix ? panel_pick(f32, NT, KB, JT, parts, norm) : stream;
+    const int groups = rule_div(NT, 14);
+    return !f32 && KB >= 192 && groups >= 192 && groups <= 256 ? panel_pick(f32, NT, KB, JT, parts, norm) : stream;
   }
   if (JT == 1 && (f32 || (stream_wide(NT, JT, parts) && KB < 96))) return stream;
   const PanelPick p = panel_pick(f32, NT, KB, JT, parts, norm);

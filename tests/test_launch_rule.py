@@ -32,6 +32,12 @@ MEASURED = [
     (True, 9, 256, 128, 2, False, 8.3, 9.5), (True, 32, 256, 128, 2, False, 12.7, 11.2),
     (True, 16, 256, 344, 2, False, 22.8, 17.9), (True, 24, 256, 344, 2, False, 27.0, 21.6),
     (True, 64, 1376, 128, 2, True, 92.3, 38.1),
+    # bf16, at most 8 rows: large matrices on both sides of the panel kernel's one-round range
+    (True, 1, 2304, 256, 2, True, 96.6, 102.4), (True, 1, 2560, 256, 2, True, 104.2, 105.9),
+    (True, 1, 2688, 256, 2, True, 113.5, 108.4), (True, 8, 3584, 256, 2, True, 139.7, 132.4),
+    (True, 1, 3200, 192, 2, True, 95.0, 90.9), (True, 1, 4608, 256, 2, True, 184.5, 209.4),
+    (True, 1, 5120, 192, 2, True, 145.8, 165.3), (True, 8, 8016, 256, 2, True, 308.2, 339.6),
+    (True, 1, 4608, 160, 2, True, 110.5, 134.0), (True, 8, 1376, 128, 2, True, 29.9, 30.1),
 ]
 
 
