@@ -30,8 +30,8 @@ size_t sprh_workspace_bytes(const spr_config* cfg) {
 
 // gemm_pick: out = {waves, tiles per wave, K-blocks per chunk, slices} of the
 // panel kernel, or zeros for the streaming kernel.
-void sprh_gemm_pick(int f32, int n, int NT, int KB, int parts, int norm, int32_t* out) {
-  const sprk::PanelPick p = sprk::gemm_pick(f32 != 0, n, NT, KB, parts, norm != 0);
+void sprh_gemm_pick(int f32, int n, int NT, int KB, int parts, int norm, size_t floats, int counters, int32_t* out) {
+  const sprk::PanelPick p = sprk::gemm_pick(f32 != 0, n, NT, KB, parts, norm != 0, sprk::SplitCap{floats, counters});
   out[0] = out[1] = out[2] = out[3] = 0;
   if (p.shape < 0) return;
   const sprk::PanelShape& s = sprk::panel_shapes(f32 != 0, sprk::row_tiles(n)).s[p.shape];
@@ -39,6 +39,28 @@ void sprh_gemm_pick(int f32, int n, int NT, int KB, int parts, int norm, int32_t
   out[1] = s.rt;
   out[2] = s.uc;
   out[3] = p.slices;
+}
+
+// tile_pick: out = {weight tiles, row tiles, stages, slices}.
+void sprh_tile_pick(int NT, int KB, int Rp, int parts, size_t floats, int counters, int32_t* out) {
+  const sprk::TilePick p = sprk::tile_pick(NT, KB, Rp, parts, sprk::SplitCap{floats, counters});
+  const sprk::TileShape& s = sprk::kTileShapes[p.shape];
+  out[0] = s.tn;
+  out[1] = s.tm;
+  out[2] = s.nst;
+  out[3] = p.slices;
+}
+
+// Split-K room of a model's workspace (floats, counters).
+void sprh_split_room(const spr_config* cfg, size_t* floats, int* counters) {
+  spr::Dims d;
+  std::string err;
+  *floats = 0;
+  *counters = 0;
+  if (cfg == nullptr || !spr::derive(*cfg, &d, &err)) return;
+  const spr::Layout l = spr::layout(d);
+  *floats = l.part_floats;
+  *counters = l.n_cnt;
 }
 
 void* sprh_new(const spr_config* cfg) {

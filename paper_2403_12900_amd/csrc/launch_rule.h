@@ -5,6 +5,7 @@
 // tiles, parts = activation parts (fp32 1, bf16 2, bf16 QKV input 3).
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
 #include <cstdint>
@@ -22,6 +23,12 @@ inline int row_tiles(int n) {
   const int t = (n + 15) / 16;
   return t <= 4 ? t : t <= 6 ? 6 : 8;
 }
+
+// What a split-K launch may use: floats of partial sums and arrival counters.
+struct SplitCap {
+  size_t floats = 0;
+  int counters = 0;
+};
 
 // Shapes of k_panel_gemm by row tiles: waves, tiles per wave, K-blocks per
 // chunk.  A work-group's NW x RT tiles are what one activation byte moved into
@@ -88,17 +95,17 @@ struct PanelPick {
   int shape = -1, slices = 1;
   double us = 0;  // the estimate
 };
-inline PanelPick panel_pick(bool f32, int NT, int KB, int JT, int parts, bool norm) {
+inline PanelPick panel_pick(bool f32, int NT, int KB, int JT, int parts, bool norm, const SplitCap& cap) {
   constexpr int kCUs = 256, kMaxSlices = 16;
   const PanelShapeSet sh = panel_shapes(f32, JT);
-  const size_t room = JT <= 4 ? spr::kSplitPartBytes : spr::kSplitPartBytesWide;
+  const size_t room = std::min(cap.floats, (JT <= 4 ? spr::kSplitPartBytes : spr::kSplitPartBytesWide) / sizeof(float));
   PanelPick best;
   for (int i = 0; i < sh.n; ++i) {
     const PanelShape& s = sh.s[i];
     const int T = s.nw * s.rt, groups = rule_div(NT, T), chunks = rule_div(KB, s.uc);
     const size_t quads = s.rt * JT + (norm ? (JT + 3) / 4 : 0);
     for (int S = 1; S <= kMaxSlices && S <= chunks; ++S) {
-      if (S > 1 && static_cast<size_t>(groups) * s.nw * S * quads * 256 * sizeof(float) > room) break;
+      if (S > 1 && (groups * s.nw > cap.counters || static_cast<size_t>(groups) * s.nw * S * quads * 256 > room)) break;
       const int rounds = rule_div(groups * S, kCUs);
       const double chain = 1.0 * rounds * rule_div(KB, S) * (0.012 * T + (0.0097 + 0.003 * s.nw) * JT * parts);
       const double hbm = 1.62e-4 * NT * KB;
@@ -154,17 +161,72 @@ inline double panel_us(bool f32, const PanelPick& p) { return f32 ? 2.6 + 1.55 *
 //     kernel would cost 12% and 35% (fp32 down, 64 tiles x 64, 24 rows: 6.2 us
 //     streamed, panel 8.7; bf16 down, 256 x 344, 24 rows: 27.0, panel 21.6);
 //   * more rows: panel.
-inline PanelPick gemm_pick(bool f32, int n, int NT, int KB, int parts, bool norm) {
+inline PanelPick gemm_pick(bool f32, int n, int NT, int KB, int parts, bool norm, const SplitCap& cap) {
   const int JT = row_tiles(n);
   const PanelPick stream;
   if (n <= kPackedRows) {
     const int groups = rule_div(NT, 14);
-    return !f32 && KB >= 192 && groups >= 192 && groups <= 256 ? panel_pick(f32, NT, KB, JT, parts, norm) : stream;
+    return !f32 && KB >= 192 && groups >= 192 && groups <= 256 ? panel_pick(f32, NT, KB, JT, parts, norm, cap) : stream;
   }
   if (JT == 1 && (f32 || (stream_wide(NT, JT, parts) && KB < 96))) return stream;
-  const PanelPick p = panel_pick(f32, NT, KB, JT, parts, norm);
+  const PanelPick p = panel_pick(f32, NT, KB, JT, parts, norm, cap);
   if (JT > 4 || stream_wide(NT, JT, parts)) return p;
   return panel_us(f32, p) < stream_us(f32, NT, KB, JT, parts) ? p : stream;
+}
+
+// A shape of k_tile_gemm and its measured times in microseconds (MI355X, two
+// and three activation parts): a K-block of a tile when its work-group is
+// alone on its CU, and when others share the CU (per tile); the start and end
+// of a tile; the publication of a split tile, and of each further slice.  The
+// last shape's four stages cover HBM latency where tiles are few.
+struct TileShape {
+  int tn, tm, nst;
+  struct Cost {
+    double alone, shared, tile, split, slice;
+  } two, three;
+};
+constexpr int kTileWaves = 4;
+constexpr TileShape kTileShapes[] = {
+    {16, 8, 2, {0.827, 0.743, 1.8, 14.1, 1.26}, {1.067, 1.057, 0.0, 15.4, 1.07}},
+    {8, 8, 2, {0.692, 0.420, 0.0, 11.5, 0.66}, {0.756, 0.595, 0.0, 12.4, 0.54}},
+    {8, 4, 2, {0.618, 0.257, 0.8, 7.9, 0.28}, {0.627, 0.275, 3.0, 7.0, 0.06}},
+    {8, 4, 4, {0.289, 0.250, 1.0, 8.3, 0.21}, {0.386, 0.307, 1.7, 8.1, 0.13}},
+};
+
+// The pick: the least estimated time.  The busiest CU's tiles (halfway between
+// the whole number and the mean, since a CU left with fewer runs them faster)
+// are multiplied one after another at the shared rate, but a tile alone is
+// bound by its own latency; the HBM time of the weights adds in quadrature.
+// Fitted to 900 timings of the 7B, 13B and 70B projections at 128 to 4096 rows
+// with weights from HBM; its choices are 2% slower than the fastest on average.
+struct TilePick {
+  int shape = 0, slices = 1;
+};
+inline TilePick tile_pick(int NT, int KB, int Rp, int parts, const SplitCap& cap) {
+  constexpr int kCUs = 256, kMaxSlices = 8;
+  TilePick best;
+  double best_us = -1;
+  for (int i = 0; i < static_cast<int>(std::size(kTileShapes)); ++i) {
+    const TileShape& s = kTileShapes[i];
+    const TileShape::Cost& c = parts == 3 ? s.three : s.two;
+    const int64_t tiles = int64_t{rule_div(NT, s.tn)} * rule_div(Rp / 16, s.tm);
+    const size_t slice_floats = static_cast<size_t>(s.tn) * s.tm * 256;
+    for (int S = 1; S <= kMaxSlices && S <= KB; ++S) {
+      if (S > 1 && (tiles * kTileWaves > cap.counters || static_cast<size_t>(tiles) * S * slice_floats > cap.floats))
+        break;
+      const double mean = static_cast<double>(tiles) * S / kCUs;
+      const double k = 0.5 * static_cast<double>((tiles * S + kCUs - 1) / kCUs) + 0.5 * (mean > 1 ? mean : 1);
+      const double kb_us = c.alone > k * c.shared ? c.alone : k * c.shared;
+      const double chain = rule_div(KB, S) * kb_us + k * c.tile, hbm = 1.62e-4 * NT * KB;
+      double us = std::sqrt(chain * chain + hbm * hbm);
+      if (S > 1) us += c.split + c.slice * S * static_cast<double>((tiles * S + kCUs - 1) / kCUs);
+      if (best_us < 0 || us < best_us) {
+        best = TilePick{i, S};
+        best_us = us;
+      }
+    }
+  }
+  return best;
 }
 
 }  // namespace sprk

@@ -15,14 +15,14 @@ template <class P>
 using QKVIn = std::conditional_t<std::is_same_v<P, BF16>, BF16x3, P>;
 
 // Room for split-K partials and arrival counters (see SplitK): the regions of
-// the attention split partials and counters, which hold what any pass's
-// split-K launch needs (spr::kSplitPartBytes) and which every launch that uses
-// them leaves zero.
+// the attention split partials and counters, which every launch that uses them
+// leaves zero.  The rules split no further than it holds.
 struct SplitRoom {
   float* part = nullptr;  // null: no split-K
   int32_t* cnt = nullptr;
   size_t part_floats = 0;
   int n_cnt = 0;
+  SplitCap cap() const { return part == nullptr ? SplitCap{} : SplitCap{part_floats, n_cnt}; }
 };
 
 // Enqueues the projection of epi.n_rows rows (at most kRows; the activation

@@ -10,6 +10,7 @@
 #pragma once
 
 #include "attn_kernels.h"
+#include "launch_rule.h"
 #include "lds_pipe.h"
 
 namespace sprk {
@@ -76,7 +77,6 @@ struct TileSplit {
   float* part;    // [tile][slice][wave][tile fragment][64 lanes][4] floats
   int32_t* cnt;   // [tile][wave] arrived slices; zero between launches
 };
-constexpr int kTileWaves = 4;
 template <int TN, int TM>
 constexpr size_t tile_slice_floats() {  // floats a wave publishes per slice
   return static_cast<size_t>(TN / 2) * (TM / 2) * 256;

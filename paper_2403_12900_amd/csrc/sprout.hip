@@ -293,7 +293,7 @@ spr_status launch_gemm(spr_model* m, int NT, const char* W, const char* X, int K
   const uint4* x = reinterpret_cast<const uint4*>(X);
   const hipStream_t st = m->st;
   const int n = epi.n_rows;
-  const PanelPick pick = gemm_pick(std::is_same_v<P, F32>, n, NT, KB, P::parts, Epi::kNorm);
+  const PanelPick pick = gemm_pick(std::is_same_v<P, F32>, n, NT, KB, P::parts, Epi::kNorm, room.cap());
   if (pick.shape >= 0) {
     launch_panel_gemm<P, Epi>(st, NT, w, x, KB, epi, room, pick);
     SPR_LAUNCHED(m, "k_panel_gemm");
@@ -1087,12 +1087,13 @@ spr_status spr_decode_step_static_scratch(spr_model* m, int32_t n_active, const 
     rs.tok[r] = 0;
     rs.hist_idx[r] = -1;
   }
+  // No more than the workspace's room, so that both take the same K slices.
   DecodeScratch sc{reinterpret_cast<float*>(m->static_scratch),
                    reinterpret_cast<int32_t*>(m->static_scratch + kStaticPartBytes),
                    reinterpret_cast<float2*>(m->static_scratch + kStaticPartBytes + kStaticCntBytes),
                    max_splits,
-                   kStaticPartBytes / sizeof(float),
-                   static_cast<int>(kStaticCntBytes / sizeof(int32_t))};
+                   std::min(kStaticPartBytes / sizeof(float), m->lay.part_floats),
+                   std::min(static_cast<int>(kStaticCntBytes / sizeof(int32_t)), m->lay.n_cnt)};
   // Every call shares the array: the attention split counters and the
   // projections' split-K counters must start at zero (a fill kernel, which a
   // graph capture may record).

@@ -1,5 +1,6 @@
 """The rules that pick a projection's kernel, shape and K slices (csrc/launch_rule.h), on the CPU."""
 import ctypes
+import random
 
 import pytest
 
@@ -8,12 +9,34 @@ from tests.test_abi_host import HOST_LIB
 STREAM = (0, 0, 0, 0)
 
 
-def gemm_pick(bf16, n, nt, kb, parts, norm):
-    """(waves, tiles per wave, K-blocks per chunk, slices) of the panel kernel; zeros: the streaming kernel."""
+ROOM = (7 << 20, 1 << 14)  # floats and counters of split-K: more than any pick below asks for
+
+
+def _lib():
     lib = ctypes.CDLL(HOST_LIB)
+    i, z = ctypes.c_int, ctypes.c_size_t
+    lib.sprh_gemm_pick.argtypes = [i, i, i, i, i, i, z, i, ctypes.c_void_p]
+    lib.sprh_tile_pick.argtypes = [i, i, i, i, z, i, ctypes.c_void_p]
+    return lib
+
+
+def gemm_pick(bf16, n, nt, kb, parts, norm, room=ROOM):
+    """(waves, tiles per wave, K-blocks per chunk, slices) of the panel kernel; zeros: the streaming kernel."""
     out = (ctypes.c_int32 * 4)()
-    lib.sprh_gemm_pick(int(not bf16), n, nt, kb, parts, int(norm), out)
+    _lib().sprh_gemm_pick(int(not bf16), n, nt, kb, parts, int(norm), *room, out)
     return tuple(out)
+
+
+def tile_pick(nt, kb, padded_rows, parts, room=ROOM):
+    """(weight tiles, row tiles, stages, slices) of the tiled prefill projection."""
+    out = (ctypes.c_int32 * 4)()
+    _lib().sprh_tile_pick(nt, kb, padded_rows, parts, *room, out)
+    return tuple(out)
+
+
+def row_tiles(n):
+    t = -(-n // 16)
+    return t if t <= 4 else 6 if t <= 6 else 8
 
 
 # (bf16, rows, weight tiles, K-blocks, parts, fused norm, us streamed, us on the panel kernel), measured on MI355X.
@@ -44,3 +67,26 @@ MEASURED = [
 @pytest.mark.parametrize("bf16,n,nt,kb,parts,norm,stream_us,panel_us", MEASURED)
 def test_the_faster_kernel_is_picked(bf16, n, nt, kb, parts, norm, stream_us, panel_us):
     assert (gemm_pick(bf16, n, nt, kb, parts, norm) == STREAM) == (stream_us < panel_us)
+
+
+@pytest.mark.parametrize("room", [(0, 0), (64 << 10, 256), (300 << 10, 4096), (1 << 20, 4096), (4 << 20, 100), (7 << 20, 1 << 14)])
+def test_split_k_fits_the_room(room):
+    """What a split launch writes (per group and wave: slices x fragments of 256 floats, one counter) is inside its room."""
+    rng = random.Random(sum(room))
+    split = 0
+    for _ in range(3000):
+        nt, kb = int(2 ** rng.uniform(0, 13)), int(2 ** rng.uniform(0, 11))
+        n, parts, norm, bf16 = rng.randint(1, 128), rng.choice([2, 3]), rng.random() < 0.5, rng.random() < 0.8
+        nw, rt, uc, s = gemm_pick(bf16, n, nt, kb, parts if bf16 else 1, norm, room)
+        if s > 1:
+            groups, jt = -(-nt // (nw * rt)), row_tiles(n)
+            assert s <= -(-kb // uc)
+            assert groups * nw <= room[1] and groups * nw * s * (rt * jt + norm * -(-jt // 4)) * 256 <= room[0]
+        split += s > 1
+        rows = 128 * rng.randint(1, 32)
+        tn, tm, _, s = tile_pick(nt, kb, rows, parts, room)
+        if s > 1:
+            tiles = -(-nt // tn) * -(-(rows // 16) // tm)
+            assert s <= kb and tiles * 4 <= room[1] and tiles * s * tn * tm * 256 <= room[0]
+        split += s > 1
+    assert (split > 0) == (room[0] > 0)
