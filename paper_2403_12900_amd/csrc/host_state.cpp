@@ -114,16 +114,15 @@ Layout layout(const Dims& d) {
   l.off_act0 = take(l.act_bytes);
   l.off_act1 = take(l.act_bytes);
   l.off_q = take(static_cast<size_t>(kPrefillRows) * d.H * d.hd * sizeof(float));
-  // Partials of decode attention's KV splits, or of the projections' split-K
-  // slices (never both in one launch).
-  // Prefill projections of full-size models split K too.
-  const bool large = d.dtype == SPR_BF16 && static_cast<int64_t>(d.nt_13) * d.kb_d * kFragBytes >= (int64_t{32} << 20);
-  l.part_floats = std::max(static_cast<size_t>(kMaxSplits) * d.H * (d.hd + 4),
-                           (large ? kPrefillPartBytes : kSplitPartBytesWide) / sizeof(float));
-  l.off_part = take(l.part_floats * sizeof(float));
-  // Arrival counters: decode attention's, one per (row, KV head), or the
-  // split-K groups'; zero between launches.
+  // Partials of decode attention's KV splits or of the projections' split-K
+  // slices (never both in one launch), and their arrival counters (attention's
+  // one per (row, KV head); zero between launches) share what kMaxSplits KV
+  // splits and attention's counters take.  The partials follow q directly: a
+  // prefill chunk's projections use both regions (see prefill_room).
+  const size_t room = (static_cast<size_t>(kMaxSplits) * d.H * (d.hd + 4) + static_cast<size_t>(kMaxRows) * d.Hkv) * 4;
   l.n_cnt = std::max(kMaxRows * d.Hkv, split_counters(d));
+  l.part_floats = (room - align256(static_cast<size_t>(l.n_cnt) * sizeof(int32_t))) / 256 * 64;
+  l.off_part = take(l.part_floats * sizeof(float));
   l.off_cnt = take(static_cast<size_t>(l.n_cnt) * sizeof(int32_t));
   l.off_amax = take(static_cast<size_t>(d.nt_lm) * kMaxRows * 2 * sizeof(float));
   l.off_prow = take(static_cast<size_t>(kPrefillRows) * 4 * sizeof(int32_t));
@@ -137,7 +136,7 @@ int split_counters(const Dims& d) {
   // Decode: one per wave of a launch, each with one tile or more, in whole
   // work-groups of at most eight waves.  Prefill: four per output tile of a
   // split launch, whose tiles are at most a few per CU.
-  return std::max({d.nt_qkv + 8, d.nt_o + 8, d.nt_13 + 8, d.nt_2 + 8, d.nt_lm + 8, 4096});
+  return std::min(kMaxSplitCounters, std::max({d.nt_qkv + 8, d.nt_o + 8, d.nt_13 + 8, d.nt_2 + 8, d.nt_lm + 8, 4096}));
 }
 
 bool static_scratch_widths(const Dims& d) { return d.nt_2 <= 2049 && d.nt_13 <= 3855 && d.nt_qkv <= 1927; }

@@ -36,13 +36,13 @@ struct Dims {
   float rope_base, eps;
 };
 
-// Bounds on what one split-K launch uses (projections of 9 rows and more):
-// partial sums in bytes, by whether the pass has at most 64 rows (every decode
-// pass) or up to 128, and arrival counters.  The launch rule keeps to them, so
-// that the same pass takes the same split in every scratch it may run in.
+// Bounds on the partial sums of one split-K launch, in bytes: a decode pass
+// (at most 64 rows), 65 to 128 rows, and a tiled prefill chunk; and the arrival
+// counters a model keeps.  The launch rules split no further than these and
+// than the scratch at hand.
 constexpr size_t kSplitPartBytes = size_t{16} << 20, kSplitPartBytesWide = size_t{28} << 20;
-// Partial sums of a prefill chunk's split-K projections (full-size models).
 constexpr size_t kPrefillPartBytes = size_t{100} << 20;
+constexpr int kMaxSplitCounters = 1 << 14;
 int split_counters(const Dims& d);
 
 // Whether spr_decode_step_static_scratch's fixed array holds the model's

@@ -54,6 +54,7 @@ static_assert(spr::kMaxRows == sprk::kRows, "decode pass size");
 // once per device at init (static_scratch_address) and passes that.
 constexpr size_t kStaticPartBytes = spr::kSplitPartBytes;
 constexpr size_t kStaticCntBytes = size_t{64} << 10;
+static_assert(spr::kMaxSplitCounters * sizeof(int32_t) <= kStaticCntBytes, "split-K counters of any model");
 constexpr size_t kStaticAmaxBytes = (size_t{8} << 20) - kStaticCntBytes;
 constexpr size_t kStaticScratchBytes = kStaticPartBytes + kStaticCntBytes + kStaticAmaxBytes;  // 24 MiB
 __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -217,10 +218,32 @@ struct DecodeScratch {
 
 DecodeScratch workspace_scratch(const spr_model* m) {
   Ptrs p{m->ws, &m->lay};
-  return DecodeScratch{p.part(), p.cnt(), p.amax(), spr::kMaxSplits, m->lay.part_floats, m->lay.n_cnt};
+  const size_t per_split = static_cast<size_t>(m->d.H) * (m->d.hd + 4);
+  const int max_splits = static_cast<int>(std::min<size_t>(spr::kMaxSplits, m->lay.part_floats / per_split));
+  return DecodeScratch{p.part(), p.cnt(), p.amax(), max_splits, m->lay.part_floats, m->lay.n_cnt};
 }
 
 SplitRoom split_room(const DecodeScratch& sc) { return SplitRoom{sc.part, sc.cnt, sc.part_floats, sc.n_cnt}; }
+
+// Split-K room of a tiled prefill projection: activation memory that is idle
+// while it runs.  QKV: the record that attention is about to write (only where
+// d_ff ends with a K-block: the rest of a last K-block of h is never written,
+// and must not hold partial sums that read as infinities).  O, gate/up and
+// down: q and the partials region behind it.
+SplitRoom prefill_room(const spr_model* m, bool qkv) {
+  Ptrs p{m->ws, &m->lay};
+  const spr::Layout& l = m->lay;
+  float* part = p.part();
+  size_t floats = l.part_floats;
+  if (!qkv) {
+    part = p.q();
+    floats += (l.off_part - l.off_q) / sizeof(float);
+  } else if (m->d.f % m->d.kblk == 0 && l.act_bytes / sizeof(float) > floats) {
+    part = reinterpret_cast<float*>(p.act(1));
+    floats = l.act_bytes / sizeof(float);
+  }
+  return SplitRoom{part, p.cnt(), std::min(floats, spr::kPrefillPartBytes / sizeof(float)), l.n_cnt};
+}
 
 template <class P>
 spr_status init_weights(spr_model* m) {
@@ -611,6 +634,7 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
   const int Rp = small ? 16 * row_tiles(C) : 128 * ceil_div(C, 128);
   const ActRec rec = act_rec(Rp);
   const SplitRoom room = split_room(workspace_scratch(m));
+  const SplitRoom qkv_room = prefill_room(m, true), mlp_room = prefill_room(m, false);
   spr_status st;
   const dim3 grid_d(ceil_div(d.d / 4, 64), C);
   k_embed_rows<QKVIn<P>><<<grid_d, 64, 0, m->st>>>(reinterpret_cast<const E*>(p.emb()), p.prow(), p.x(),
@@ -649,12 +673,12 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
         // Query tiles take hi + mid of the three-part record (and the larger
         // two-part tiles), key and value tiles all three parts.
         const int q_tiles = d.H * d.hd / 16;
-        tile_gemm<P, EpiQKVRows<P, KP>, 3>(m->st, p.wqkv(l), p.act(0), q_tiles, d.kb_d, Rp, e, room);
+        tile_gemm<P, EpiQKVRows<P, KP>, 3>(m->st, p.wqkv(l), p.act(0), q_tiles, d.kb_d, Rp, e, qkv_room);
         e.nt_base = q_tiles;
         const char* wkv = p.wqkv(l) + static_cast<size_t>(q_tiles) * d.kb_d * 64 * sizeof(uint4);
-        tile_gemm<QKVIn<P>>(m->st, wkv, p.act(0), d.nt_qkv - q_tiles, d.kb_d, Rp, e, room);
+        tile_gemm<QKVIn<P>>(m->st, wkv, p.act(0), d.nt_qkv - q_tiles, d.kb_d, Rp, e, qkv_room);
       } else {
-        tile_gemm<QKVIn<P>>(m->st, p.wqkv(l), p.act(0), d.nt_qkv, d.kb_d, Rp, e, room);
+        tile_gemm<QKVIn<P>>(m->st, p.wqkv(l), p.act(0), d.nt_qkv, d.kb_d, Rp, e, qkv_room);
       }
     }
     if (d.hd == 128) {
@@ -664,16 +688,16 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
     }
     {
       EpiResidRows<P> e{C, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      tile_gemm<P>(m->st, p.wo(l), p.act(1), d.nt_o, d.kb_o, Rp, e, room);
+      tile_gemm<P>(m->st, p.wo(l), p.act(1), d.nt_o, d.kb_o, Rp, e, mlp_room);
     }
     launch_row_rscale(m, C);
     {
       EpiSwiGLURows<P> e{C, rec, p.rs(), reinterpret_cast<E*>(p.act(1))};
-      tile_gemm<P>(m->st, p.w13(l), p.act(0), d.nt_13, d.kb_d, Rp, e, room);
+      tile_gemm<P>(m->st, p.w13(l), p.act(0), d.nt_13, d.kb_d, Rp, e, mlp_room);
     }
     {  // the new residual is the next layer's QKV input (the prompt's last rows reach the LM head from x)
       EpiResidRows<QKVIn<P>> e{C, d.d, rec, p.x(), reinterpret_cast<E*>(p.act(0))};
-      tile_gemm<P>(m->st, p.w2(l), p.act(1), d.nt_2, d.kb_f, Rp, e, room);
+      tile_gemm<P>(m->st, p.w2(l), p.act(1), d.nt_2, d.kb_f, Rp, e, mlp_room);
     }
     SPR_LAUNCHED(m, "prefill layer");
   }
@@ -1070,7 +1094,7 @@ spr_status spr_decode_step_static_scratch(spr_model* m, int32_t n_active, const 
   const int max_splits = static_cast<int>(std::min<size_t>(spr::kMaxSplits, kStaticPartBytes / per_split));
   if (static_cast<size_t>(spr::kMaxRows) * d.Hkv * sizeof(int32_t) > kStaticCntBytes ||
       static_cast<size_t>(d.nt_lm) * spr::kMaxRows * sizeof(float2) > kStaticAmaxBytes || max_splits < n_active ||
-      !spr::static_scratch_widths(d) || spr::split_counters(d) * sizeof(int32_t) > kStaticCntBytes)
+      !spr::static_scratch_widths(d))
     return fail(SPR_ERR_INVALID_ARG, "decode_step_static_scratch: the model or batch exceeds the 24 MiB static "
                                      "scratch (at most 128 KV heads, vocab <= 130048, n_heads * (head_dim + 4) "
                                      "* 4 * n_active <= 16 MiB, d_ff <= 30840 and (n_heads + 2 * n_kv_heads) * "
