@@ -123,9 +123,11 @@ TOY_CASES = {
     "bf16_mha32_splits_fit_resident": (
         ModelConfig(n_layers=1, d_model=256, n_heads=32, n_kv_heads=32, head_dim=64, d_ff=128, vocab=300),
         [140 + (i % 5) for i in range(24)], [3] * 24),
-    # Split-K past 8 rows with slices of unequal length: d = 4160 (130 K-blocks: QKV and O slices
-    # of 32 and 33) and d_ff = 6208 (194: down slices of 48 and 49).  At 17-20 rows QKV, O, gate/up
-    # and down split; at 9-16 QKV and down; at 1-8 none.  13 query heads per KV head.
+    # Split-K past 8 rows, on the panel kernel, with slices of unequal length: O (130 K-blocks, three
+    # slices: 44, 44 and 42 K-blocks at 9-16 rows, 42, 44 and 44 at 17-20), down (194, five slices of
+    # 38 and 40) and the LM head (130, six or seven slices); QKV's five are equal (26), and six-tile
+    # groups leave one with query and key tiles both.  Gate/up does not split, and at 1-8 rows nothing
+    # does.  13 query heads per KV head.
     "bf16_split_k_uneven_slices": (
         ModelConfig(n_layers=1, d_model=4160, n_heads=65, n_kv_heads=5, head_dim=64, d_ff=6208, vocab=600),
         [(5 * i) % 23 + 1 for i in range(20)], [2] * 4 + [3] * 4 + [5, 6] * 6),

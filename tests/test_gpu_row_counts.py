@@ -1,7 +1,8 @@
-"""Projections at the edges of their row ranges: the streaming kernel ends at 8 rows, and the panel kernel changes its
-row-tile count at 16, 32, 48, 64 and (prefill chunks) 96 and 128 rows.  The model's widths leave remainders everywhere:
-7 and 10 K-blocks (no multiple of a chunk's 2 or 4, and fewer than three chunks), 14, 25 and 21 weight tiles (no multiple
-of a work-group's), query tiles that end inside a work-group."""
+"""Projections at the edges of their row ranges, in a model so narrow that passes of up to 64 rows take the streaming
+kernel: packed up to 8 rows, then one row tile more at 17, 33 and 49 rows.  Prefill chunks of 65 to 128 rows take the panel
+kernel (one tile per wave, K whole) with six and eight row tiles, larger ones and all fp32 ones the tiled kernel.  The
+model's widths leave remainders everywhere: 7 and 10 K-blocks (no multiple of a pipeline stage or of four waves), 14, 25
+and 21 weight tiles (no multiple of a work-group's)."""
 import numpy as np
 import pytest
 
