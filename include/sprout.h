@@ -155,10 +155,10 @@ spr_status spr_decode_step(spr_model* m, int32_t n_active, const int32_t* slots,
  * before the step.  Every call on one device shares that device's array:
  * calls that overlap on one device (on different streams, or from different
  * threads) race and must not be issued.  SPR_ERR_INVALID_ARG when the model
- * or batch does not fit the array: more than 128 KV heads, a vocabulary
- * above 130048, n_heads * (head_dim + 4) * 4 bytes * n_active above 16 MiB,
- * or d_ff or (n_heads + 2 * n_kv_heads) * head_dim above 30840; other
- * errors as spr_decode_step.
+ * or batch does not fit the array (more than 128 KV heads, a vocabulary
+ * above 130048, n_heads * (head_dim + 4) * 4 bytes * n_active above 16 MiB)
+ * or is wider than the call takes (d_model above 32784, d_ff or (n_heads + 2
+ * * n_kv_heads) * head_dim above 30840); other errors as spr_decode_step.
  */
 spr_status spr_decode_step_static_scratch(spr_model* m, int32_t n_active, const int32_t* slots, const int32_t* lens,
                                           int32_t* tok, float* logits, int32_t* retired);

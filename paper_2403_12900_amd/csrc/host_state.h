@@ -45,9 +45,10 @@ constexpr size_t kPrefillPartBytes = size_t{100} << 20;
 constexpr int kMaxSplitCounters = 1 << 14;
 int split_counters(const Dims& d);
 
-// Whether spr_decode_step_static_scratch's fixed array holds the model's
-// widths: the limits of the entry point (d_model 32784, d_ff 30840, query, key
-// and value rows 30840).
+// Whether spr_decode_step_static_scratch takes the model's widths: limits of
+// the entry point (d_model 32784, d_ff 30840, query, key and value rows 30840)
+// that its array no longer sets -- the launch rules split no further than it
+// holds, at any width -- and that callers may rely on.
 bool static_scratch_widths(const Dims& d);
 
 struct Layout {

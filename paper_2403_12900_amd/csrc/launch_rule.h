@@ -57,7 +57,7 @@ template <>
 struct PanelShapes<false, 4> {
   static constexpr PanelShape s[] = {{4, 1, 2}, {8, 1, 2}, {4, 2, 2}, {6, 2, 2}, {7, 2, 2}};
 };
-// fp32 models (no full-size fp32 model is served): one shape.
+// fp32: one shape, for two row tiles or more (one row tile is streamed).
 template <int JT>
 struct PanelShapes<true, JT> {
   static constexpr PanelShape s[] = {{4, 1, 1}};
@@ -87,10 +87,13 @@ inline PanelShapeSet panel_shapes(bool f32, int JT) {
 // with the HBM time of the matrix, plus the publication of the slices.  Its
 // choices are on average 2% slower than the fastest.  More than one work-group
 // per CU is priced up by 5% each (512 tiles x 256 K-blocks, 14 rows: 768
-// work-groups 30 us, 192 take 23.5).  Slices of
-// 64 K-blocks of 256-K-block tiles are priced up: every work-group then
-// starts at a multiple of 64 KiB (512 tiles x 256 K-blocks, 14 rows: four
-// slices 31 us, three 23.5 us).
+// work-groups 30 us, 192 take 24).  Slices of a multiple of 64 K-blocks in
+// tiles of a multiple of 256 are priced up by a quarter, since all work-groups
+// then start at multiples of 64 KiB and the slices of a tile at fractions of a
+// power of two (in groups of 8 tiles, four slices against three: 512 tiles x
+// 256 K-blocks, 14 rows 28.4 us / 24.1, 32 rows 32.0 / 27.2; of 4 tiles, 256 x
+// 512, 14 rows 26.8 / 25.4).  Two slices of 128 lose less than that, but are
+// never the best there; tiles of 128 K-blocks in two slices of 64 lose nothing.
 struct PanelPick {
   int shape = -1, slices = 1;
   double us = 0;  // the estimate
@@ -152,7 +155,7 @@ inline double panel_us(bool f32, const PanelPick& p) { return f32 ? 2.6 + 1.55 *
 //     2304 x 256 102 / 97 and 2560 x 256 106 / 104 (CUs left idle), 4608 x 256
 //     209 / 185, 5120 x 192 165 / 146 and 8016 x 256 (an LM head) 340 / 306 (a
 //     second round), 1376 x 128 30.2 / 29.7; 3840 x 160 equal;
-//   * one row tile of fp32: streaming (the panel kernel took 1.2 to 2.9 times
+//   * one row tile (9 to 16 rows) of fp32: streaming (the panel kernel took 1.2 to 2.9 times
 //     as long, but for 300 tiles x 260 K-blocks, 26.3 us against 27.6);
 //   * one row tile of bf16 in the wide form: streaming below 96 K-blocks (9
 //     rows, 2000 tiles x 64: 21.1 us, panel 26.0; 1024 x 96: 18.4, panel 17.8);

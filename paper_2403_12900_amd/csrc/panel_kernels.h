@@ -1,6 +1,7 @@
-// Projection for 17 to 128 token rows (decode passes past 16 rows, prefill of
-// short prompts): y[b][n] = sum_k W[n][k] x[b][k], with the op that follows
-// fused into the epilogue.
+// Projection for up to 128 token rows (decode passes past 8 rows and prompt
+// chunks of at most 128, where gemm_pick finds it faster than streaming, and a
+// few large matrices at any row count): y[b][n] = sum_k W[n][k] x[b][k], with
+// the op that follows fused into the epilogue.
 //
 // At these row counts a projection is still bound by its weight stream, but
 // every work-group needs the activations of its K range too: with the

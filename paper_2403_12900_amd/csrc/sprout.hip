@@ -13,7 +13,8 @@
 //     k_stream_gemm<EpiResid>    x += h W2^T (and the next QKV input)
 //   k_stream_gemm<EpiLogits>     RMSNorm(x) Wlm^T, per-tile greedy candidates
 //   k_argmax_final               tok[slot] = lowest index of the row maximum
-// (past 8 rows the projections run as k_panel_gemm / k_panel_gemm_qkv).
+// (past 8 rows the projections run as k_panel_gemm / k_panel_gemm_qkv where
+// that is the faster kernel, see gemm_pick).
 // A prefill chunk (up to 4096 prompt rows of one or more requests) runs the
 // same layer stack on tiled, compute-bound kernels:
 //   k_embed_rows; per layer k_row_rscale, k_tile_gemm<EpiQKVRows> (query
@@ -49,9 +50,10 @@ static_assert(spr::kMaxRows == sprk::kRows, "decode pass size");
 // Scratch of spr_decode_step_static_scratch: a fixed array in device memory,
 // one per device that loads the library, held until the process ends.
 // Regions: split partials (of attention, or of the projections' split-K
-// slices), arrival counters, LM-head greedy candidates.  Host code never passes the array's name to a kernel (on the
-// host it is only a stand-in symbol): it resolves the array's device address
-// once per device at init (static_scratch_address) and passes that.
+// slices), arrival counters, LM-head greedy candidates.  Host code never
+// passes the array's name to a kernel (on the host it is only a stand-in
+// symbol): it resolves the array's device address once per device at init
+// (static_scratch_address) and passes that.
 constexpr size_t kStaticPartBytes = spr::kSplitPartBytes;
 constexpr size_t kStaticCntBytes = size_t{64} << 10;
 static_assert(spr::kMaxSplitCounters * sizeof(int32_t) <= kStaticCntBytes, "split-K counters of any model");
@@ -670,8 +672,8 @@ spr_status prefill_pass(spr_model* m, const PrefillChunk& ch, int32_t* tok, floa
       e.rs = p.rs();
       e.nt_base = 0;
       if constexpr (QKVIn<P>::parts == 3) {
-        // Query tiles take hi + mid of the three-part record (and the larger
-        // two-part tiles), key and value tiles all three parts.
+        // Query tiles take hi + mid of the three-part record, key and value
+        // tiles all three parts.
         const int q_tiles = d.H * d.hd / 16;
         tile_gemm<P, EpiQKVRows<P, KP>, 3>(m->st, p.wqkv(l), p.act(0), q_tiles, d.kb_d, Rp, e, qkv_room);
         e.nt_base = q_tiles;
@@ -1096,9 +1098,9 @@ spr_status spr_decode_step_static_scratch(spr_model* m, int32_t n_active, const 
       static_cast<size_t>(d.nt_lm) * spr::kMaxRows * sizeof(float2) > kStaticAmaxBytes || max_splits < n_active ||
       !spr::static_scratch_widths(d))
     return fail(SPR_ERR_INVALID_ARG, "decode_step_static_scratch: the model or batch exceeds the 24 MiB static "
-                                     "scratch (at most 128 KV heads, vocab <= 130048, n_heads * (head_dim + 4) "
-                                     "* 4 * n_active <= 16 MiB, d_ff <= 30840 and (n_heads + 2 * n_kv_heads) * "
-                                     "head_dim <= 30840)");
+                                     "scratch or the call's limits (at most 128 KV heads, vocab <= 130048, n_heads * "
+                                     "(head_dim + 4) * 4 * n_active <= 16 MiB, d_model <= 32784, d_ff <= 30840 and "
+                                     "(n_heads + 2 * n_kv_heads) * head_dim <= 30840)");
   std::string err;
   if ((st = m->tab.check_decode(n_active, slots, lens, &err)) != SPR_OK) return fail(st, err);
   RowSet rs;
