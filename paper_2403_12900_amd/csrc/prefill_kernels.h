@@ -56,14 +56,15 @@ __global__ __launch_bounds__(64) void k_embed_rows(const typename P::elem* __res
 // multiply.  Weight tiles past NT re-read tile NT - 1 and row tiles past Rp
 // re-read the last one; neither is stored.
 //
-// What bounds it (MI355X, 4096 rows of the 7B gate/up projection): its MFMAs
-// alone take about 770 us, its loads alone 560 (256 x 256) to 800 us (128 x
-// 128), and they overlap only across work-groups, since within one every wave
-// waits at the same barrier.  So a shape is chosen for two or more work-groups
-// per CU -- two stages of 256 features x 128 rows are 64 KiB of LDS (80 KiB
-// with three parts) -- instead of one larger work-group with deeper stages:
-// 4096 rows of O (7B) take 188 us (1460 TFLOP/s issued) against 262 us for one
-// eight-wave 256 x 256 work-group of three stages.
+// What bounds it (MI355X, 4096 rows of the 7B gate/up projection, in a six-
+// layer prefill): 1140 us, of which its LDS reads and MFMAs alone take 925 and
+// its loads alone 687.  The two overlap only across work-groups, since within
+// one every wave waits at the same barrier.  So a shape is chosen for two or
+// more work-groups per CU -- two stages of 256 features x 128 rows are 64 KiB
+// of LDS (80 KiB with three parts) -- instead of one larger work-group with
+// deeper stages: 4096 rows of O (7B) take 188 us launched alone (1460 TFLOP/s
+// issued), 217 us in a prefill, against 262 and 265 us for one eight-wave 256 x
+// 256 work-group of three stages.
 //
 // K is split over gridDim.z slices (kSplit) where the tiles alone leave the
 // chip idle: each wave publishes its partial sums with agent-coherent stores
